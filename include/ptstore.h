@@ -109,7 +109,7 @@ enum {
      * then the smallest id, and raises L to that block's H. What stays
      * resident is therefore always a set of whole prefixes. New blocks take
      * never-used ids first, then the freed ids from the smallest up; blocks
-     * still without an id are refused as without this flag. Costs 44 bytes
+     * still without an id are refused as without this flag. Costs 40 bytes
      * of device memory per pool block. */
     PTSTORE_FLAG_EVICT = 8u,
     /* Name a new block in an insert's batch table by its key and only the

@@ -420,15 +420,12 @@ size_t carve_evict(void* base, int64_t capacity, EvictView* ev) {
     };
     ev->freq = static_cast<uint64_t*>(take(cap * 8));
     ev->prio = static_cast<uint64_t*>(take(cap * 8));
-    ev->live = static_cast<int32_t*>(take(cap * 4));
     ev->prot = static_cast<int32_t*>(take(cap * 4));
     ev->depth = static_cast<int32_t*>(take(cap * 4));
     ev->nkey = static_cast<uint64_t*>(take(cap * 8));
     ev->spos = static_cast<uint32_t*>(take(cap * 4));
     ev->victims = static_cast<int32_t*>(take(cap * 4));
     ev->wmask = static_cast<uint64_t*>(take(words * 8));
-    ev->wcnt = static_cast<uint32_t*>(take(words * 4));
-    ev->wbase = static_cast<uint32_t*>(take(words * 4));
     ev->hist = static_cast<uint32_t*>(take((size_t)kSelPasses * kSelBins * 4));
     ev->part = static_cast<uint64_t*>(take((size_t)kSelGroups * 8 * 8));
     ev->words = words;

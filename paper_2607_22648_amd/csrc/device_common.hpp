@@ -54,11 +54,13 @@ struct alignas(128) CounterSlot {
     unsigned long long pad[12];
 };
 
-// Eviction threshold search: at most this many digit passes of kSelBits bits
-// each over a key of at most 128 bits.
+// Eviction threshold search: digits of kSelBits bits over a key of at most
+// 128. The first kSelPasses digits are found over all candidates, the rest
+// over the few that agree with them.
 constexpr int kSelBits = 11;
 constexpr int kSelBins = 1 << kSelBits;
-constexpr int kSelPasses = (128 + kSelBits - 1) / kSelBits;
+constexpr int kSelPasses = 2;
+constexpr int kSelDone = kSelPasses + 1;
 
 // Device-side counters and status of a store.
 struct DevState {
@@ -88,7 +90,8 @@ struct DevState {
     unsigned long long sel_hi, sel_lo;  // threshold key found so far (left-aligned)
     unsigned long long sel_need;        // rank of the threshold among what matches it
     unsigned int sel_range_done;        // workgroups finished the range pass
-    unsigned int sel_done[kSelPasses];  // workgroups finished per digit pass
+    unsigned int sel_done[kSelDone];    // workgroups finished per digit pass
+    unsigned int sel_list;              // candidates listed after those passes
     // what the search ranks: 0 = eviction candidates (ids below sel_hi_id
     // that the batch did not match, key (H, deeper, id)); 1 = the host tier,
     // ids sel_lo_id .. sel_hi_id-1, key (H descending, id)
@@ -223,6 +226,42 @@ __device__ inline uint64_t window_chain(uint64_t c, uint64_t carry, const ChainC
         if (lane >= d) s = addmod61(s, sp);
     }
     return mulmod61(cc.pow0, addmod61(mulmod61(cc.p, carry), s));
+}
+
+// Scans and reductions over the wave with data-parallel moves (row_shr 1, 2,
+// 4, 8 inside rows of 16 lanes, then row_bcast 15 and 31 across them): each
+// step is one VALU operation, where a shuffle is an LDS round trip. Called
+// with every lane active.
+template <int CTRL, int ROWS>
+__device__ inline uint32_t dpp(uint32_t identity, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)x, CTRL, ROWS, 0xF, false);
+}
+template <typename Op>
+__device__ inline uint32_t row_scan(uint32_t x, uint32_t identity, Op op) {  // inclusive, rows of 16
+    x = op(x, dpp<0x111, 0xF>(identity, x));
+    x = op(x, dpp<0x112, 0xF>(identity, x));
+    x = op(x, dpp<0x114, 0xF>(identity, x));
+    return op(x, dpp<0x118, 0xF>(identity, x));
+}
+template <typename Op>
+__device__ inline uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {  // inclusive
+    x = row_scan(x, identity, op);
+    x = op(x, dpp<0x142, 0xA>(identity, x));
+    return op(x, dpp<0x143, 0xC>(identity, x));
+}
+__device__ inline uint32_t wave_scan_add(uint32_t x) {
+    return wave_scan(x, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ inline uint32_t read_lane(uint32_t x, int lane) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+}
+// The sum of the 16 per-wave values in LDS that come before wave wv's, and
+// of all of them (a workgroup of 16 waves).
+__device__ inline uint32_t waves_before(const uint32_t* wsum, int wv, uint32_t* total) {
+    const uint32_t x = row_scan(wsum[threadIdx.x & 15], 0u, [](uint32_t a, uint32_t b) { return a + b; });
+    *total = read_lane(x, 15);
+    const int w = __builtin_amdgcn_readfirstlane(wv);
+    return w == 0 ? 0u : read_lane(x, w - 1);
 }
 
 __device__ inline unsigned long long ballot64(bool p) { return __ballot(p); }

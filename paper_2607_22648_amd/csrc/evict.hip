@@ -22,15 +22,24 @@
 // takes the minimum and maximum of each field over the candidates; the key
 // then keeps only the bits in which candidates can differ,
 //   (H - Hmin) | (depth_max - depth) | (id - id_min),
-// left-aligned in 128 bits (typically some 40 bits wide). Each digit pass
-// is a 2048-bin histogram of the next 11 bits among the keys that agree with
-// the threshold found so far; the last workgroup of a pass to finish picks
-// the digit. Then the victims are marked in a bit mask, their index slots
-// become tombstones, their parents lose a child, L takes their largest H,
-// and a scan lists them by ascending id, the order in which their ids are
-// reused. When deleted slots have piled up, the index is rebuilt from the
-// surviving blocks.
+// left-aligned in 128 bits (typically some 40 bits wide). Two digit passes
+// over all candidates, each a 2048-bin histogram of the next 11 bits among
+// the keys that agree with the threshold found so far, whose last workgroup
+// to finish picks the digit; then the candidates that agree in those 22 bits
+// are listed, and the last workgroup finds the remaining digits over the
+// list alone. Then the victims are marked in a bit mask, their index slots
+// become tombstones, L takes their largest H, and a scan lists them by
+// ascending id, the order in which their ids are reused. When deleted slots
+// have piled up, the index is cleared instead and publish enters the
+// surviving blocks again.
+//
+// The work of a search is small (16 bytes per candidate and pass); what it
+// costs is launches, about 4.6 us each. Six here, where the twelve digit
+// passes, most of them empty, the scan, the list and two rebuild steps had
+// made seventeen. A store of up to 16,384 blocks runs none of this: see
+// evict_small.hpp.
 #include "kernels.hpp"
+#include "evict_small.hpp"
 
 namespace ptsd {
 namespace {
@@ -38,8 +47,6 @@ namespace {
 constexpr int kThreads = 256;
 
 typedef unsigned __int128 u128;
-
-__device__ inline unsigned bit_width(uint64_t x) { return x ? 64u - (unsigned)__clzll((long long)x) : 0u; }
 
 // Is `id` ranked by the running search? (sel_lo_id <= id < sel_hi_id holds.)
 __device__ inline bool sel_candidate(const EvictView& ev, const DevState* st, int64_t id) {
@@ -73,8 +80,11 @@ __device__ inline T wave_reduce(T v, Op op, int lane) {
 // Ranges of H, depth and id over the candidates, their number, and from them
 // the key layout. Also clears the digit histograms. Each workgroup writes its
 // own partial (no shared-address atomics); the last one to finish combines
-// them. Serves both searches (eviction and hot set, see sel_key).
-__global__ __launch_bounds__(kThreads) void k_sel_range(EvictView ev, DevState* st) {
+// them. Serves both searches (eviction and hot set, see sel_key); an
+// eviction's victims are counted here, so that whether the index is rebuilt
+// is known before they are marked.
+__global__ __launch_bounds__(kThreads) void k_sel_range(EvictView ev, DevState* st, int64_t capacity,
+                                                        uint64_t slots_n) {
     if (st->ev_want == 0) return;  // uniform over the grid
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < (int64_t)kSelPasses * kSelBins;
@@ -130,6 +140,8 @@ __global__ __launch_bounds__(kThreads) void k_sel_range(EvictView ev, DevState* 
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
+    if (!st->sel_hot)
+        evict_account(st, capacity, slots_n, tot[6] < st->ev_want ? tot[6] : st->ev_want);
     if (tot[6] <= st->ev_want) {  // every candidate goes
         st->ev_all = 1;
         return;
@@ -211,13 +223,71 @@ __global__ __launch_bounds__(kThreads) void k_sel_pass(EvictView ev, DevState* s
     }
 }
 
-// Marks the victims (one bit per id), deletes their index entries, takes a
-// child from their parents and raises the clock to their largest priority.
+// The digits past the first kSelPasses: the candidates that agree with the
+// threshold so far are listed (their ids, in the array the victims come into
+// later), and the last workgroup finds the rest over the list by itself.
+// The list is short -- in practice the blocks of one H and about one depth
+// -- and a list as long as the store only makes this one workgroup slower.
+constexpr int kFinishThreads = 1024;
+
+__global__ __launch_bounds__(kFinishThreads) void k_sel_finish(EvictView ev, DevState* st) {
+    if (st->ev_want == 0 || st->ev_all || st->sel_npass <= (unsigned)kSelPasses) return;  // uniform
+    __shared__ uint32_t h[kSelBins];
+    __shared__ uint32_t wsum[kFinishThreads / kWave], found[2];
+    __shared__ int last;
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+    const int64_t lo_id = (int64_t)st->sel_lo_id, hi_id = (int64_t)st->sel_hi_id;
+    u128 thr = ((u128)st->sel_hi << 64) | (u128)st->sel_lo;
+    constexpr int kKnown = 128 - kSelBits * kSelPasses;  // key bits still open
+    for (int64_t base = lo_id + (int64_t)blockIdx.x * kFinishThreads; base < hi_id;
+         base += (int64_t)gridDim.x * kFinishThreads) {
+        const int64_t id = base + t;
+        const bool in = id < hi_id && sel_candidate(ev, st, id) &&
+                        (sel_key(ev, st, id) >> kKnown) == (thr >> kKnown);
+        const unsigned long long mask = ballot64(in);
+        unsigned at = 0;
+        if (lane == 0 && mask) at = atomicAdd(&st->sel_list, (unsigned)__popcll(mask));
+        at = (unsigned)__shfl((int)at, 0, kWave);
+        if (in) ev.victims[at + __popcll(mask & lanes_below(lane))] = (int32_t)id;
+    }
+    __threadfence();
+    __syncthreads();
+    if (t == 0) last = atomicAdd(&st->sel_done[kSelPasses], 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    const unsigned n = __hip_atomic_load(&st->sel_list, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t need = (uint32_t)st->sel_need;
+    h[2 * t] = h[2 * t + 1] = 0;
+    __syncthreads();
+    for (int pass = kSelPasses; pass < (int)st->sel_npass; ++pass) {
+        const int hi_bit = 128 - kSelBits * pass;
+        const int lo_bit = hi_bit - kSelBits > 0 ? hi_bit - kSelBits : 0;
+        const unsigned dmask = (1u << (hi_bit - lo_bit)) - 1u;
+        for (unsigned i = t; i < n; i += kFinishThreads) {
+            const int32_t id = __hip_atomic_load(&ev.victims[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const u128 k = sel_key(ev, st, id);
+            if ((k >> hi_bit) == (thr >> hi_bit)) atomicAdd(&h[(unsigned)(k >> lo_bit) & dmask], 1u);
+        }
+        uint32_t before;
+        const unsigned digit = small_digit(h, wsum, found, need, &before);
+        thr |= (u128)digit << lo_bit;
+        need -= before;
+    }
+    if (t == 0) {
+        st->sel_hi = (uint64_t)(thr >> 64);
+        st->sel_lo = (uint64_t)thr;
+    }
+}
+
+// Marks the victims (one bit per id), takes them out of the index and raises
+// the clock to their largest priority. An index to be rebuilt is cleared
+// instead.
 __global__ __launch_bounds__(kThreads) void k_ev_mark(EvictView ev, DevState* st, Slot* slots,
-                                                      const int32_t* parent) {
+                                                      uint64_t slots_n) {
     if (st->ev_want == 0) return;
     const int lane = threadIdx.x & (kWave - 1);
-    const bool all = st->ev_all != 0;
+    const bool all = st->ev_all != 0, rebuild = st->ev_rebuild != 0;
     const u128 thr = ((u128)st->sel_hi << 64) | (u128)st->sel_lo;
     const int64_t old = (int64_t)st->insert_old_count;
     const int64_t span = ev.words * kWave;
@@ -231,26 +301,16 @@ __global__ __launch_bounds__(kThreads) void k_ev_mark(EvictView ev, DevState* st
             if (sel) {
                 const uint64_t hp = ev.prio[id];
                 maxp = hp > maxp ? hp : maxp;
-                slots[ev.spos[id]].key = kTombKey;
-                const int32_t p = parent[id];
-                if (p >= 0) atomicSub(&ev.live[p], 1);
-                if (ev.tier.rep_of && id >= ev.tier.owned) {  // its replica goes too
-                    const int64_t h = id - ev.tier.owned;
-                    const int32_t slot = ev.tier.rep_of[h];
-                    if (slot >= 0) {
-                        ev.tier.rep_of[h] = -1;
-                        ev.tier.rep_id[slot] = -1;
-                        atomicSub(&st->rep_count, 1ull);
-                    }
-                }
+                drop_victim(ev, st, slots, id, rebuild);
             }
         }
         const unsigned long long mask = ballot64(sel);
-        if (lane == 0 && id / kWave < ev.words) {
-            ev.wmask[id / kWave] = mask;
-            ev.wcnt[id / kWave] = (uint32_t)__popcll(mask);
-        }
+        if (lane == 0 && id / kWave < ev.words) ev.wmask[id / kWave] = mask;
     }
+    if (rebuild)
+        for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < slots_n;
+             i += (uint64_t)gridDim.x * kThreads)
+            slots[i] = empty_slot();
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         const uint64_t o = shfl_u64(maxp, lane ^ d);
@@ -259,120 +319,42 @@ __global__ __launch_bounds__(kThreads) void k_ev_mark(EvictView ev, DevState* st
     if (lane == 0 && maxp) atomicMax(&st->clock, (unsigned long long)maxp);
 }
 
-// One workgroup: exclusive scan of the per-word victim counts; updates the
-// eviction counters and decides whether the index is rebuilt.
-__global__ __launch_bounds__(1024) void k_ev_scan(EvictView ev, DevState* st, int64_t capacity,
-                                                  uint64_t slots_n) {
-    if (st->ev_want == 0) {
-        if (threadIdx.x == 0) st->ev_rebuild = 0;
-        return;
-    }
-    __shared__ long long part[1024];
-    const int64_t W = ev.words;
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int64_t per = (W + nt - 1) / nt;
-    const int64_t lo = min(W, (int64_t)t * per), hi = min(W, lo + per);
-    long long s = 0;
-    for (int64_t i = lo; i < hi; ++i) s += ev.wcnt[i];
-    part[t] = s;
-    __syncthreads();
-    for (int d = 1; d < nt; d <<= 1) {
-        long long v = t >= d ? part[t - d] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    long long run = part[t] - s;
-    for (int64_t i = lo; i < hi; ++i) {
-        ev.wbase[i] = (uint32_t)run;
-        run += ev.wcnt[i];
-    }
-    if (t == nt - 1) {
-        const unsigned long long nv = (unsigned long long)part[nt - 1];
-        const unsigned long long fresh = (unsigned long long)capacity - st->insert_old_count;
-        st->ev_nv = nv;
-        st->evictions += nv;
-        if (st->ev_new > fresh + nv) {
-            st->full_events += 1;
-            st->insert_full = 1;
-        }
-        const unsigned long long tomb = st->tombstones + nv;
-        if (tomb * 4 > slots_n) {
-            st->ev_rebuild = 1;
-            st->rebuilds += 1;
-            st->tombstones = 0;
-        } else {
-            st->ev_rebuild = 0;
-            st->tombstones = tomb;
-        }
-    }
-}
+// One workgroup: lists the victims by ascending id, from the bit mask in
+// tiles of 1024 x 4 words.
+constexpr int kListPer = 4;
 
-// Lists the victims by ascending id.
-__global__ __launch_bounds__(kThreads) void k_ev_list(EvictView ev, DevState* st) {
+__global__ __launch_bounds__(1024) void k_ev_list(EvictView ev, DevState* st) {
     if (st->ev_want == 0) return;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t span = ev.words * kWave;
-    for (int64_t id = (int64_t)blockIdx.x * kThreads + threadIdx.x; id < span;
-         id += (int64_t)gridDim.x * kThreads) {
-        const int64_t w = id / kWave;
-        const uint64_t mask = ev.wmask[w];
-        if ((mask >> lane) & 1ull) ev.victims[ev.wbase[w] + __popcll(mask & lanes_below(lane))] = (int32_t)id;
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void k_rebuild_clear(DevState* st, Slot* slots, uint64_t n) {
-    if (!st->ev_rebuild) return;
-    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kThreads) {
-        Slot z;
-        z.key = kEmptyKey;
-        z.id = -1;
-        z.parent = -1;
-        slots[i] = z;
-    }
-}
-
-// Re-enters every surviving block into the cleared index.
-__global__ __launch_bounds__(kThreads) void k_rebuild_insert(EvictView ev, DevState* st, Slot* slots,
-                                                             uint64_t slot_mask, const int32_t* parent,
-                                                             const HashTables* ht) {
-    if (!st->ev_rebuild) return;
-    const int64_t old = (int64_t)st->insert_old_count;
-    for (int64_t id = (int64_t)blockIdx.x * kThreads + threadIdx.x; id < old;
-         id += (int64_t)gridDim.x * kThreads) {
-        if ((ev.wmask[id / kWave] >> (id & (kWave - 1))) & 1ull) continue;  // evicted
-        const uint64_t ik = ev.nkey[id];
-        uint64_t pos = slot_of(ik, ht->slot_seed, slot_mask);
-        // at most half the slots hold blocks, so an empty one is always found
-        for (uint64_t step = 0; step <= slot_mask; ++step) {
-            const unsigned long long prev =
-                atomicCAS(reinterpret_cast<unsigned long long*>(&slots[pos].key), kEmptyKey,
-                          (unsigned long long)ik);
-            if (prev == kEmptyKey) {
-                slots[pos].id = (int32_t)id;
-                slots[pos].parent = parent[id];
-                ev.spos[id] = (uint32_t)pos;
-                break;
-            }
-            pos = (pos + 1) & slot_mask;
+    __shared__ uint32_t wsum[1024 / kWave];
+    const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < ev.words; base += 1024 * kListPer) {
+        const int64_t w0 = base + t * kListPer;
+        uint64_t m[kListPer];
+        uint32_t s = 0;
+#pragma unroll
+        for (int k = 0; k < kListPer; ++k) {
+            m[k] = w0 + k < ev.words ? ev.wmask[w0 + k] : 0ull;
+            s += (uint32_t)__popcll(m[k]);
         }
-    }
-}
-
-// Accesses of the resident paths of an insert's requests (after its
-// evictions, with the clock they left).
-__global__ __launch_bounds__(kThreads) void k_touch(EvictView ev, DevState* st, const int32_t* m,
-                                                    const int32_t* ids, int32_t R, int32_t max_blocks) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
-    if (r >= R) return;
-    const uint64_t L = st->clock;
-    const int32_t n = m[r];
-    const int32_t* row = ids + r * max_blocks;
-    for (int32_t b = lane; b < n; b += kWave) {
-        const int32_t id = row[b];
-        const uint64_t f = atomicAdd((unsigned long long*)&ev.freq[id], 1ull) + 1ull;
-        atomicMax((unsigned long long*)&ev.prio[id], (unsigned long long)(L + f));
+        uint32_t x = s;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)x, d, kWave);
+            if (lane >= d) x += y;
+        }
+        if (lane == kWave - 1) wsum[wv] = x;
+        __syncthreads();
+        uint32_t at = carry + x - s;
+        for (int w = 0; w < 1024 / kWave; ++w) {
+            const uint32_t ws = wsum[w];
+            if (w < wv) at += ws;
+            carry += ws;
+        }
+#pragma unroll
+        for (int k = 0; k < kListPer; ++k)
+            for (uint64_t b = m[k]; b; b &= b - 1)
+                ev.victims[at++] = (int32_t)((w0 + k) * kWave + __ffsll((long long)b) - 1);
+        __syncthreads();  // wsum is written again by the next tile
     }
 }
 
@@ -387,8 +369,9 @@ __global__ __launch_bounds__(kThreads) void k_touch(EvictView ev, DevState* st, 
 
 __global__ void k_rep_setup(DevState* st, TierView tier) {
     const int t = threadIdx.x;
-    if (t < kSelPasses) st->sel_done[t] = 0;
+    if (t < kSelDone) st->sel_done[t] = 0;
     if (t != 0) return;
+    st->sel_list = 0;
     const uint64_t count = st->count;
     st->sel_hot = 1;
     st->sel_lo_id = (uint64_t)tier.owned;
@@ -508,31 +491,33 @@ unsigned grid_for(int64_t n, int64_t cap_groups) {
 
 }  // namespace
 
-hipError_t launch_evict(const IndexView& ix, const InsertTarget& tgt, const EvictView& ev,
-                        hipStream_t s) {
+namespace {
+// The threshold search over `n` ids at most (the range is in the state).
+hipError_t launch_search(const EvictView& ev, DevState* st, int64_t n, int64_t capacity,
+                         uint64_t slots_n, hipStream_t s) {
     hipError_t e;
     // about four candidates per thread: few workgroups add to the same bins
-    const unsigned g = grid_for((tgt.capacity + 3) / 4, kSelGroups);
-    hipLaunchKernelGGL(k_sel_range, dim3(g), dim3(kThreads), 0, s, ev, ix.state);
+    const unsigned g = grid_for((n + 3) / 4, kSelGroups);
+    hipLaunchKernelGGL(k_sel_range, dim3(g), dim3(kThreads), 0, s, ev, st, capacity, slots_n);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int p = 0; p < kSelPasses; ++p) {
-        hipLaunchKernelGGL(k_sel_pass, dim3(g), dim3(kThreads), 0, s, ev, ix.state, p);
+        hipLaunchKernelGGL(k_sel_pass, dim3(g), dim3(kThreads), 0, s, ev, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const unsigned gw = grid_for(ev.words * kWave, 2048);
-    hipLaunchKernelGGL(k_ev_mark, dim3(gw), dim3(kThreads), 0, s, ev, ix.state, tgt.slots,
-                       (const int32_t*)tgt.parent);
+    hipLaunchKernelGGL(k_sel_finish, dim3((g + 3) / 4), dim3(kFinishThreads), 0, s, ev, st);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_evict(const IndexView& ix, const InsertTarget& tgt, const EvictView& ev,
+                        hipStream_t s) {
+    if (evicts_in_rank(tgt.capacity)) return hipSuccess;  // done by the insert's rank kernel
+    hipError_t e = launch_search(ev, ix.state, tgt.capacity, tgt.capacity, ix.slot_mask + 1, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ev_mark, dim3(grid_for(ev.words * kWave, 2048)), dim3(kThreads), 0, s, ev,
+                       ix.state, tgt.slots, ix.slot_mask + 1);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ev_scan, dim3(1), dim3(1024), 0, s, ev, ix.state, tgt.capacity,
-                       ix.slot_mask + 1);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ev_list, dim3(gw), dim3(kThreads), 0, s, ev, ix.state);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rebuild_clear, dim3(grid_for((int64_t)(ix.slot_mask + 1), 2048)), dim3(kThreads),
-                       0, s, ix.state, tgt.slots, ix.slot_mask + 1);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rebuild_insert, dim3(g), dim3(kThreads), 0, s, ev, ix.state, tgt.slots,
-                       ix.slot_mask, (const int32_t*)tgt.parent, ix.ht);
+    hipLaunchKernelGGL(k_ev_list, dim3(1), dim3(1024), 0, s, ev, ix.state);
     return hipGetLastError();
 }
 
@@ -542,26 +527,13 @@ hipError_t launch_replicate(const IndexView& ix, const EvictView& ev, const Copy
     const TierView& t = ev.tier;
     hipLaunchKernelGGL(k_rep_setup, dim3(1), dim3(64), 0, s, ix.state, t);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const unsigned g = grid_for((t.host_blocks + 3) / 4, kSelGroups);
-    hipLaunchKernelGGL(k_sel_range, dim3(g), dim3(kThreads), 0, s, ev, ix.state);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int k = 0; k < kSelPasses; ++k) {
-        hipLaunchKernelGGL(k_sel_pass, dim3(g), dim3(kThreads), 0, s, ev, ix.state, k);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    if ((e = launch_search(ev, ix.state, t.host_blocks, 0, 0, s)) != hipSuccess) return e;
     const unsigned gw = grid_for(((t.host_blocks + kWave - 1) / kWave) * kWave, 2048);
     hipLaunchKernelGGL(k_rep_diff, dim3(gw), dim3(kThreads), 0, s, ev, ix.state);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_rep_assign, dim3(1), dim3(1024), 0, s, ev, ix.state);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return launch_copy_rows(p, t.copies, &ix.state->rep_new, t.replicas, s);
-}
-
-hipError_t launch_touch_paths(const IndexView& ix, const EvictView& ev, const int32_t* m,
-                              const int32_t* ids, int32_t R, int32_t max_blocks, hipStream_t s) {
-    const unsigned grid = (unsigned)((R + (kThreads / kWave) - 1) / (kThreads / kWave));
-    hipLaunchKernelGGL(k_touch, dim3(grid), dim3(kThreads), 0, s, ev, ix.state, m, ids, R, max_blocks);
-    return hipGetLastError();
 }
 
 }  // namespace ptsd

@@ -8,50 +8,63 @@
 // order, and a block already created by an earlier request of the batch is
 // reused. The GPU gets there without serialising requests or blocks:
 //
-//   lookup     match every request against the store as it was (m0, ids)
-//   hash_all   chained keys of every block (the key of block b is a function
-//              of the whole prefix up to b)
-//   claim      wave per request, lane per missing block b >= m0: the block
-//              claims or joins the batch-table entry named by (key, depth)
-//              and records in it the smallest request that needs it; the
-//              block that claims an entry also records its depth there
-//   verify     wave per request, lane per block: the entry must hold the
-//              block's depth (else blocks of two depths, possibly of one
-//              request, share it), and the entry's smallest request o must
-//              hold the same prefix. It does if block b's tokens are
-//              equal and either b is both requests' first missing block under
-//              the same stored parent, or both requests' blocks b-1 sit in
-//              the same entry (by induction, equal prefixes). Any failure --
-//              a collision of names between different prefixes -- raises a
-//              flag.
-//   exact      only when the flag is up: the table is cleared and rebuilt one
-//              block after another per request, each block named exactly by
-//              (entry of its parent, its tokens); slower, same result
-//   count      per request, the blocks it is the first (smallest r) to need
-//   scan       exclusive scan of the counts -> rank base per request; the
-//              store count advances, clipped at capacity
-//   assign     new id = old count + base[r] + rank within r (wave ballot);
-//              ids at or beyond capacity are refused (children rank after
-//              parents, so what is refused is always a suffix of a path)
-//   publish    ids / created / m_out, block metadata, index slots
+//   match      match every request against the store as it was (m0, ids) and
+//              write the chained keys of all its blocks (the key of block b is
+//              a function of the whole prefix up to b); empties the batch
+//              table on the side (lookup.hip, kInsert)
+//   claim      lane per missing block b >= m0: the block claims or joins the
+//              batch-table entry named by (key, depth) and records in it the
+//              smallest request that needs it; the block that claims an entry
+//              also records its depth there
+//   verify     lane per block: the entry must hold the block's depth (else
+//              blocks of two depths, possibly of one request, share it), and
+//              the entry's smallest request o must hold the same prefix. It
+//              does if block b's tokens are equal and either b is both
+//              requests' first missing block under the same stored parent, or
+//              both requests' blocks b-1 sit in the same entry (by induction,
+//              equal prefixes). Any failure -- a collision of names between
+//              different prefixes -- raises a flag. The same pass counts, per
+//              request, the blocks it is the first (smallest r) to need
+//   rank       one workgroup. Only when the flag is up it first redoes the
+//              claim exactly: the table is cleared and rebuilt one block after
+//              another per request, each block named by (entry of its parent,
+//              its tokens); slower, same result. Then the exclusive scan of
+//              the counts gives every request its first rank; the store count
+//              advances, clipped at capacity
+//   publish    lane per block: id, created, m_out, block metadata, index slot
+//
+// Ranks need no per-block pass: whoever needs a block also needs its parent,
+// so the blocks a request is the first to need are its last cnt[r] ones, and
+// its block b has rank start[r] + b with start[r] = (scan of the counts) -
+// (its first such block). The new id is old count + rank; ids at or beyond
+// capacity are refused (children rank after parents, so what is refused is
+// always a suffix of a path).
 //
 // Ids come from a scan, never from an atomic counter, so they are
 // deterministic and equal the sequential ones.
 //
-// With eviction on, count also marks the blocks the batch matched
-// (protected), scan computes how many blocks must be evicted, evict.hip
-// frees them between scan and assign, assign hands out never-used ids and
-// then the freed ones, publish may take a deleted index slot, and the
-// resident paths are accessed last.
+// What bounds a call is the number of dependent launches, about 4.6 us each
+// for batches of up to a few hundred requests, not the work in them. Hence
+// five kernels (without eviction, or with a small store's, all of whose
+// eviction runs inside rank), where lookup, key hashing, two table clears,
+// claim, exact claim, verify, count, scan, assign, publish and touch had
+// been launches of their own; each wave has one 64-block window of one
+// request, so that a request of many windows is not walked by one wave.
+//
+// With eviction on, verify also marks the blocks the batch matched
+// (protected), rank computes how many blocks must be evicted and frees them
+// (a small store; a larger one in the kernels of evict.hip between rank and
+// publish), publish hands out never-used ids and then the freed ones, may
+// take a deleted index slot, and accesses the resident paths.
 #include "kernels.hpp"
+#include "evict_small.hpp"
 
 namespace ptsd {
 
 struct alignas(16) BatchEntry {
     unsigned long long word;  // claim: tag of (key, depth); exact: (parent label << 32) | token position
     int32_t owner;            // smallest request that needs this block
-    int32_t node_id;          // claim to verify: depth of the claiming block (exact path: -1);
-                              // from assign on: id assigned, -1 if refused
+    int32_t depth;            // depth of the claiming block (exact claim: -1)
 };
 
 namespace {
@@ -60,50 +73,50 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr uint32_t kStoreLabel = 0x80000000u;  // parent label of a stored block: bit 31 | (id + 1)
 
-__device__ inline unsigned long long lanes_below(int lane) {
-    return lane == 0 ? 0ull : (~0ull >> (64 - lane));
-}
-
-// Clears the batch table. The first clear of an insert (only_if_collision =
-// 0) also lowers the collision flag; the second runs only if it was raised.
-// The insert's first kernel (only_if_collision = 0) also advances the
-// eviction epoch, so that a replayed capture marks its own matches.
-__global__ void k_table_clear(BatchEntry* __restrict__ t, uint64_t n, unsigned int* collision,
-                              int only_if_collision, DevState* st, int ev_on) {
-    if (only_if_collision && *collision == 0) return;
-    if (!only_if_collision && blockIdx.x == 0 && threadIdx.x == 0) {
-        *collision = 0;
-        if (ev_on) {  // protection marks are compared with it; 0 marks nothing
-            const unsigned long long e = st->ev_epoch + 1;
-            st->ev_epoch = e >= 0x7FFFFFFFull ? 1ull : e;
-        }
-    }
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (uint64_t)gridDim.x * blockDim.x) {
-        BatchEntry e;
-        e.word = kEmptyKey;
-        e.owner = 0x7FFFFFFF;
-        e.node_id = -1;
-        t[i] = e;
-    }
+// A block's tokens move four at a time where all addresses allow it (block
+// sizes that are multiples of 4, requests that start on 16 bytes), sixteen
+// in flight: a token per step, each waiting for the one before, had been
+// half of publish.
+__device__ inline bool by_fours(const int32_t* a, const int32_t* b, int bt) {
+    return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0 && (bt & 3) == 0;
 }
 
 __device__ inline bool same_tokens(const int32_t* __restrict__ a, const int32_t* __restrict__ b, int bt) {
+    if (by_fours(a, b, bt)) {
+        const int4* x = reinterpret_cast<const int4*>(a);
+        const int4* y = reinterpret_cast<const int4*>(b);
+        bool eq = true;
+        for (int i = 0; i < bt / 4; i += 4) {
+            int4 u[4], w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {  // past the end: the last piece again
+                u[j] = x[min(i + j, bt / 4 - 1)];
+                w[j] = y[min(i + j, bt / 4 - 1)];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                eq &= (u[j].x == w[j].x) & (u[j].y == w[j].y) & (u[j].z == w[j].z) & (u[j].w == w[j].w);
+        }
+        return eq;
+    }
     for (int i = 0; i < bt; ++i)
         if (a[i] != b[i]) return false;
     return true;
 }
 
-// Blocks of request r considered by this batch (0 for a malformed request).
-__device__ inline int32_t n_blocks(const Batch& bat, int64_t r, int bt, int64_t* o0) {
-    int64_t a = bat.offsets[r], e = bat.offsets[r + 1];
-    if (a < 0 || e < a || e > bat.n_tokens) {
-        *o0 = 0;
-        return 0;
+__device__ inline void copy_tokens(int32_t* __restrict__ dst, const int32_t* __restrict__ src, int bt) {
+    if (by_fours(dst, src, bt)) {
+        for (int i = 0; i < bt / 4; i += 4) {
+            int4 u[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) u[j] = reinterpret_cast<const int4*>(src)[min(i + j, bt / 4 - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i + j < bt / 4) reinterpret_cast<int4*>(dst)[i + j] = u[j];
+        }
+        return;
     }
-    *o0 = a;
-    int64_t n = (e - a) / bt;
-    return (int32_t)(n < bat.max_blocks ? n : bat.max_blocks);
+    for (int i = 0; i < bt; ++i) dst[i] = src[i];
 }
 
 // Name of a new block in the batch table: its chained key and its depth
@@ -134,176 +147,223 @@ __device__ inline void count_cas(const InsertArgs& a, unsigned long long cas,
     wave_count(&cs->cas_failures, fails, lane);
 }
 
+// Windows of 64 blocks a request has room for.
+__host__ __device__ inline int64_t windows(int32_t max_blocks) { return (max_blocks + kWave - 1) / kWave; }
+
+// One wave per (request, window).
+struct WaveOf {
+    int64_t r;
+    int32_t b, w;  // this lane's block, the window
+    int lane;
+    bool any;      // the request exists
+};
+__device__ inline WaveOf wave_of(const Batch& bat) {
+    WaveOf v;
+    v.lane = threadIdx.x & (kWave - 1);
+    const int64_t nw = windows(bat.max_blocks);
+    const int64_t i = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
+    v.r = i / nw;
+    v.w = (int32_t)(i - v.r * nw);
+    v.b = v.w * kWave + v.lane;
+    v.any = v.r < bat.R;
+    return v;
+}
+
 __global__ __launch_bounds__(kThreads) void k_claim(InsertArgs a) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
-    if (r >= a.bat.R) return;
-    const int64_t maxb = a.bat.max_blocks;
-    int64_t o0;
-    const int32_t n = n_blocks(a.bat, r, a.ix.block_tokens, &o0);
-    const int32_t m0 = a.sc.m0[r];
+    const WaveOf v = wave_of(a.bat);
+    if (!v.any) return;
+    const int64_t i = v.r * a.bat.max_blocks + v.b;
+    const int32_t b = v.b;
+    const bool mine = b >= a.sc.m0[v.r] && b < a.sc.nblk[v.r];
+    if (!ballot64(mine)) return;
     BatchEntry* __restrict__ tab = reinterpret_cast<BatchEntry*>(a.sc.table);
     unsigned long long cas = 0, fails = 0;
-    for (int32_t w0 = m0; w0 < n; w0 += kWave) {
-        const int32_t b = w0 + lane;
-        if (b >= n) continue;
-        const unsigned long long tag = tag_of(a.sc.keys[r * maxb + b], b, *a.ix.ht);
+    if (mine) {
+        const unsigned long long tag = tag_of(a.sc.keys[i], b, *a.ix.ht);
         uint64_t pos = tag & a.sc.table_mask;
         while (true) {
             const unsigned long long prev = atomicCAS(&tab[pos].word, kEmptyKey, tag);
             ++cas;
             if (prev == kEmptyKey) {
-                tab[pos].node_id = b;  // read by verify, kernels later
+                tab[pos].depth = b;  // read by verify, a kernel later
                 break;
             }
             if (prev == tag) break;
             ++fails;
             pos = (pos + 1) & a.sc.table_mask;
         }
-        atomicMin(&tab[pos].owner, (int32_t)r);
-        a.sc.label[r * maxb + b] = (int32_t)pos;
+        atomicMin(&tab[pos].owner, (int32_t)v.r);
+        a.sc.label[i] = (int32_t)pos;
     }
-    count_cas(a, cas, fails, lane);
+    count_cas(a, cas, fails, v.lane);
 }
 
 __global__ __launch_bounds__(kThreads) void k_verify(InsertArgs a) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
-    if (r >= a.bat.R) return;
+    const WaveOf v = wave_of(a.bat);
+    if (!v.any) return;
     const int bt = a.ix.block_tokens;
-    const int64_t maxb = a.bat.max_blocks;
-    int64_t o0;
-    const int32_t n = n_blocks(a.bat, r, bt, &o0);
-    const int32_t m0 = a.sc.m0[r];
+    const int64_t maxb = a.bat.max_blocks, r = v.r;
+    const int32_t b = v.b, m0 = a.sc.m0[r], n = a.sc.nblk[r];
+    if (a.ev.on && b < m0)  // a block this request matched: not evicted by this insert
+        a.ev.prot[a.ids[r * maxb + b]] = (int32_t)a.ix.state->ev_epoch;
+    if (v.w * kWave + kWave <= m0 || v.w * kWave >= n) return;  // no new block in the window
     const BatchEntry* __restrict__ tab = reinterpret_cast<const BatchEntry*>(a.sc.table);
-    bool ok = true;
-    for (int32_t w0 = m0; w0 < n; w0 += kWave) {
-        const int32_t b = w0 + lane;
-        if (b >= n) continue;
-        const BatchEntry te = tab[a.sc.label[r * maxb + b]];
-        if (te.node_id != b) {  // the entry was claimed at another depth
-            ok = false;
-            continue;
-        }
+    bool ok = true, own = false;
+    if (b >= m0 && b < n) {
+        const int32_t label = a.sc.label[r * maxb + b];
+        const BatchEntry te = tab[label];
         const int64_t o = te.owner;
-        if (o == r) continue;
-        int64_t oo0;
-        const int32_t on = n_blocks(a.bat, o, bt, &oo0);
-        const int32_t om0 = a.sc.m0[o];
-        bool good = b < on && b >= om0 &&
-                    same_tokens(a.bat.tokens + oo0 + (int64_t)b * bt, a.bat.tokens + o0 + (int64_t)b * bt, bt);
-        if (good) {
-            if (b == m0)
-                good = om0 == b && (b == 0 || a.ids[o * maxb + b - 1] == a.ids[r * maxb + b - 1]);
-            else
-                good = om0 <= b - 1 && a.sc.label[o * maxb + b - 1] == a.sc.label[r * maxb + b - 1];
+        own = o == r;
+        ok = te.depth == b;  // else the entry was claimed at another depth
+        if (ok && !own) {
+            const int32_t om0 = a.sc.m0[o];
+            ok = b < a.sc.nblk[o] && b >= om0 &&
+                 same_tokens(a.bat.tokens + a.bat.offsets[o] + (int64_t)b * bt,
+                             a.bat.tokens + a.bat.offsets[r] + (int64_t)b * bt, bt);
+            if (ok) {
+                if (b == m0)
+                    ok = om0 == b && (b == 0 || a.ids[o * maxb + b - 1] == a.ids[r * maxb + b - 1]);
+                else
+                    ok = om0 <= b - 1 && a.sc.label[o * maxb + b - 1] == a.sc.label[r * maxb + b - 1];
+            }
         }
-        ok &= good;
     }
     if (!ok) *a.sc.collision = 1;
+    const int c = __popcll(ballot64(own));
+    if (v.lane == 0 && c) atomicAdd(&a.sc.cnt[r], c);
 }
 
-// Exact claim, one block after another per request (runs only on a collision).
-__global__ __launch_bounds__(kThreads) void k_claim_exact(InsertArgs a) {
-    if (*a.sc.collision == 0) return;
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r == 0) atomicAdd(&a.ix.state->insert_fallbacks, 1ull);
-    if (r >= a.bat.R) return;
+// The exact claim, by one workgroup: one block after another per request
+// (runs only on a collision). Labels, owners and counts are made anew. The
+// entries and counts are changed by device-scope atomics, so what an earlier
+// plain read left in the compute unit's cache is dropped between the steps.
+__device__ inline void claim_exact(const InsertArgs& a) {
+    const int t = threadIdx.x, nt = blockDim.x;
     const int bt = a.ix.block_tokens;
     const int64_t maxb = a.bat.max_blocks;
-    int64_t o0;
-    const int32_t n = n_blocks(a.bat, r, bt, &o0);
-    const int32_t m0 = a.sc.m0[r];
     BatchEntry* __restrict__ tab = reinterpret_cast<BatchEntry*>(a.sc.table);
     const HashTables* __restrict__ ht = a.ix.ht;
-    uint32_t plabel = m0 == 0 ? kStoreLabel : (kStoreLabel | (uint32_t)(a.ids[r * maxb + m0 - 1] + 1));
-    for (int32_t b = m0; b < n; ++b) {
-        const uint64_t ik = index_key(a.sc.keys[r * maxb + b], *ht);
-        const uint32_t tpos = (uint32_t)(o0 + (int64_t)b * bt);
-        const unsigned long long word = ((unsigned long long)plabel << 32) | tpos;
-        uint64_t pos = slot_of(ik, ~ht->slot_seed, a.sc.table_mask);
-        while (true) {
-            const unsigned long long prev = atomicCAS(&tab[pos].word, kEmptyKey, word);
-            if (prev == kEmptyKey) break;
-            if ((uint32_t)(prev >> 32) == plabel &&
-                same_tokens(a.bat.tokens + (uint32_t)prev, a.bat.tokens + tpos, bt))
-                break;
-            pos = (pos + 1) & a.sc.table_mask;
-        }
-        atomicMin(&tab[pos].owner, (int32_t)r);
-        a.sc.label[r * maxb + b] = (int32_t)pos;
-        plabel = (uint32_t)pos;
+    if (t == 0) atomicAdd(&a.ix.state->insert_fallbacks, 1ull);
+    for (uint64_t i = t; i <= a.sc.table_mask; i += nt) {
+        BatchEntry e;
+        e.word = kEmptyKey;
+        e.owner = 0x7FFFFFFF;
+        e.depth = -1;
+        tab[i] = e;
     }
-}
-
-__global__ __launch_bounds__(kThreads) void k_count(InsertArgs a) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
-    if (r >= a.bat.R) return;
-    const int64_t maxb = a.bat.max_blocks;
-    int64_t o0;
-    const int32_t n = n_blocks(a.bat, r, a.ix.block_tokens, &o0);
-    const BatchEntry* __restrict__ tab = reinterpret_cast<const BatchEntry*>(a.sc.table);
-    if (a.ev.on) {  // the blocks this request matched cannot be evicted by this insert
-        const int32_t epoch = (int32_t)a.ix.state->ev_epoch;
-        for (int32_t b = lane; b < a.sc.m0[r]; b += kWave) a.ev.prot[a.ids[r * maxb + b]] = epoch;
-    }
-    int32_t c = 0;
-    for (int32_t w0 = a.sc.m0[r]; w0 < n; w0 += kWave) {
-        const int32_t b = w0 + lane;
-        const bool mine = b < n && tab[a.sc.label[r * maxb + b]].owner == (int32_t)r;
-        c += __popcll(ballot64(mine));
-    }
-    if (lane == 0) a.sc.cnt[r] = c;
-}
-
-// One workgroup: exclusive scan of cnt into base, then advance the count.
-__global__ __launch_bounds__(1024) void k_scan(InsertArgs a) {
-    __shared__ long long part[1024];
-    const int R = a.bat.R;
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int per = (R + nt - 1) / nt;
-    const int lo = min(R, t * per), hi = min(R, lo + per);
-    long long s = 0;
-    for (int i = lo; i < hi; ++i) s += a.sc.cnt[i];
-    part[t] = s;
+    for (int64_t r = t; r < a.bat.R; r += nt) a.sc.cnt[r] = 0;
+    __threadfence();
     __syncthreads();
-    // Hillis-Steele inclusive scan over the per-thread sums
-    for (int d = 1; d < nt; d <<= 1) {
-        long long v = t >= d ? part[t - d] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
+    for (int64_t r = t; r < a.bat.R; r += nt) {
+        const int32_t n = a.sc.nblk[r], m0 = a.sc.m0[r];
+        const int64_t o0 = a.bat.offsets[r];
+        uint32_t plabel = m0 == 0 ? kStoreLabel : (kStoreLabel | (uint32_t)(a.ids[r * maxb + m0 - 1] + 1));
+        for (int32_t b = m0; b < n; ++b) {
+            const uint64_t ik = index_key(a.sc.keys[r * maxb + b], *ht);
+            const uint32_t tpos = (uint32_t)(o0 + (int64_t)b * bt);
+            const unsigned long long word = ((unsigned long long)plabel << 32) | tpos;
+            uint64_t pos = slot_of(ik, ~ht->slot_seed, a.sc.table_mask);
+            while (true) {
+                const unsigned long long prev = atomicCAS(&tab[pos].word, kEmptyKey, word);
+                if (prev == kEmptyKey) break;
+                if ((uint32_t)(prev >> 32) == plabel &&
+                    same_tokens(a.bat.tokens + (uint32_t)prev, a.bat.tokens + tpos, bt))
+                    break;
+                pos = (pos + 1) & a.sc.table_mask;
+            }
+            atomicMin(&tab[pos].owner, (int32_t)r);
+            a.sc.label[r * maxb + b] = (int32_t)pos;
+            plabel = (uint32_t)pos;
+        }
     }
-    long long run = part[t] - s;
-    for (int i = lo; i < hi; ++i) {
-        a.sc.base[i] = (int32_t)run;
-        run += a.sc.cnt[i];
+    __threadfence();
+    __syncthreads();
+    for (int64_t r = t; r < a.bat.R; r += nt) {
+        int32_t c = 0;
+        for (int32_t b = a.sc.m0[r]; b < a.sc.nblk[r]; ++b)
+            c += __hip_atomic_load(&tab[a.sc.label[r * maxb + b]].owner, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT) == (int32_t)r;
+        a.sc.cnt[r] = c;
     }
+    __threadfence();
+    __syncthreads();
+}
+
+// One workgroup: every request's start rank and the store count. The
+// requests go in tiles of 1024 x 4, four neighbouring counts per thread, as
+// in the copies' list; a batch has at most 2^29 blocks, so every sum fits in
+// 32 bits. A small store's eviction follows in the same workgroup.
+constexpr int kRankThreads = 1024;
+constexpr int kRankPer = 4;
+
+template <bool EVICT_SMALL>
+__global__ __launch_bounds__(kRankThreads) void k_rank(InsertArgs a) {
+    __shared__ uint32_t wsum[kRankThreads / kWave];
     DevState* st = a.ix.state;
-    if (a.ev.on && t < kSelPasses) st->sel_done[t] = 0;  // fresh selection state for evict.hip
-    if (t == nt - 1) {
-        const long long total = part[nt - 1];
-        const long long old = (long long)st->count;
-        const long long cap = a.tgt.capacity;
+    const int R = a.bat.R;
+    const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
+    // every load that does not wait for another goes out together: the flag,
+    // the state, the first tile's counts and a small store's blocks
+    const unsigned int collision = *a.sc.collision;
+    const long long old = (long long)st->count;
+    const int32_t epoch = EVICT_SMALL ? (int32_t)st->ev_epoch : 0;
+    const unsigned long long tombstones = EVICT_SMALL ? st->tombstones : 0ull;
+    uint32_t v[kRankPer], n[kRankPer];
+    auto load_counts = [&](int i0) {
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            v[k] = i0 + k < R ? (uint32_t)a.sc.cnt[i0 + k] : 0u;
+            n[k] = i0 + k < R ? (uint32_t)a.sc.nblk[i0 + k] : 0u;
+        }
+    };
+    load_counts(t * kRankPer);
+    SmallBlocks blocks;
+    if (EVICT_SMALL) load_blocks(a.ev, a.tgt.capacity, &blocks);
+    if (collision) {  // uniform
+        claim_exact(a);
+        load_counts(t * kRankPer);
+    }
+    uint32_t carry = 0;
+    for (int base = 0; base < R; base += kRankThreads * kRankPer) {
+        const int i0 = base + t * kRankPer;
+        if (base) load_counts(i0);
+        uint32_t s = 0;
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) s += v[k];
+        const uint32_t x = wave_scan_add(s);
+        if (lane == kWave - 1) wsum[wv] = x;
+        __syncthreads();
+        uint32_t total;
+        uint32_t run = carry + waves_before(wsum, wv, &total) + x - s;
+        carry += total;
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            if (i0 + k < R) a.sc.start[i0 + k] = (int32_t)(run - (n[k] - v[k]));
+            run += v[k];
+        }
+        __syncthreads();  // wsum is written again by the next tile
+    }
+    const long long total = carry;
+    const long long cap = a.tgt.capacity;
+    const long long want = total - (cap - old);  // ids the batch needs beyond the never-used ones
+    __syncthreads();                             // every wave has read the count
+    if (t == 0) {
         st->insert_old_count = (unsigned long long)old;
         st->insert_full = 0;
-        if (old + total > cap) {
-            if (!a.ev.on) {  // with eviction: decided once victims are known
-                st->full_events += 1;
-                st->insert_full = 1;
-            }
-            st->count = (unsigned long long)cap;
-        } else {
-            st->count = (unsigned long long)(old + total);
+        if (want > 0 && !a.ev.on) {  // with eviction: decided once victims are known
+            st->full_events += 1;
+            st->insert_full = 1;
         }
+        st->count = (unsigned long long)(want > 0 ? cap : old + total);
         if (a.ev.on) {
-            const long long want = total - (cap - old);
             st->ev_new = (unsigned long long)total;
             st->ev_want = want > 0 ? (unsigned long long)want : 0ull;
             st->ev_all = 0;
             st->ev_nv = 0;
+            st->ev_rebuild = 0;
             st->sel_range_done = 0;
+            st->sel_list = 0;
+            for (int k = 0; k < kSelDone; ++k) st->sel_done[k] = 0;
             st->sel_npass = 0;
             st->sel_hot = 0;
             st->sel_lo_id = 0;
@@ -313,126 +373,126 @@ __global__ __launch_bounds__(1024) void k_scan(InsertArgs a) {
             st->sel_need = st->ev_want;
         }
     }
+    if (!EVICT_SMALL || want <= 0) return;  // uniform
+    __syncthreads();  // the state above is read below
+    evict_small(a.ev, st, a.tgt.slots, a.ix.slot_mask + 1, a.tgt.capacity, old, want, epoch,
+                tombstones, blocks);
 }
 
-__global__ __launch_bounds__(kThreads) void k_assign(InsertArgs a) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
-    if (r >= a.bat.R) return;
-    const int64_t maxb = a.bat.max_blocks;
-    int64_t o0;
-    const int32_t n = n_blocks(a.bat, r, a.ix.block_tokens, &o0);
-    BatchEntry* __restrict__ tab = reinterpret_cast<BatchEntry*>(a.sc.table);
-    const long long old = (long long)a.ix.state->insert_old_count;
-    const long long fresh = a.tgt.capacity - old;                        // never-used ids
-    const long long nv = a.ev.on ? (long long)a.ix.state->ev_nv : 0;    // freed ids
-    long long run = a.sc.base[r];  // rank among the batch's new blocks
-    for (int32_t w0 = a.sc.m0[r]; w0 < n; w0 += kWave) {
-        const int32_t b = w0 + lane;
-        BatchEntry* e = b < n ? &tab[a.sc.label[r * maxb + b]] : nullptr;
-        const bool mine = e && e->owner == (int32_t)r;
-        const unsigned long long mask = ballot64(mine);
-        if (mine) {
-            const long long k = run + __popcll(mask & lanes_below(lane));
-            int32_t id = -1;
-            if (k < fresh)
-                id = (int32_t)(old + k);
-            else if (k - fresh < nv)
-                id = a.ev.victims[k - fresh];
-            e->node_id = id;
-            if (a.ev.on && id >= 0) {  // a new block starts unaccessed, with no resident child
-                a.ev.freq[id] = 0;
-                a.ev.prio[id] = 0;
-                a.ev.live[id] = 0;
-                a.ev.prot[id] = 0;
-                a.ev.depth[id] = b;
+// Re-enters into the index, cleared by the eviction, every block that
+// survived it; the batch's new blocks are entered at the same time (each by
+// its own compare-and-swap on an empty slot, in any order).
+__device__ inline void reenter_survivors(const InsertArgs& a) {
+    const int64_t old = (int64_t)a.ix.state->insert_old_count;
+    for (int64_t id = (int64_t)blockIdx.x * kThreads + threadIdx.x; id < old;
+         id += (int64_t)gridDim.x * kThreads) {
+        if ((a.ev.wmask[id / kWave] >> (id & (kWave - 1))) & 1ull) continue;  // evicted
+        const uint64_t ik = a.ev.nkey[id];
+        uint64_t pos = slot_of(ik, a.ix.ht->slot_seed, a.ix.slot_mask);
+        // at most half the slots hold blocks, so an empty one is always found
+        for (uint64_t step = 0; step <= a.ix.slot_mask; ++step) {
+            const unsigned long long prev =
+                atomicCAS(reinterpret_cast<unsigned long long*>(&a.tgt.slots[pos].key), kEmptyKey,
+                          (unsigned long long)ik);
+            if (prev == kEmptyKey) {
+                a.tgt.slots[pos].id = (int32_t)id;
+                a.tgt.slots[pos].parent = a.tgt.parent[id];
+                a.ev.spos[id] = (uint32_t)pos;
+                break;
             }
+            pos = (pos + 1) & a.ix.slot_mask;
         }
-        run += __popcll(mask);
     }
+}
+
+// The id of a request's new block b, whose entry in the batch table is
+// `label`: -1 if it is refused.
+__device__ inline int32_t new_id(const InsertArgs& a, int32_t label, int32_t b, long long old,
+                                 long long fresh, long long nv, int32_t* owner) {
+    const BatchEntry* __restrict__ tab = reinterpret_cast<const BatchEntry*>(a.sc.table);
+    *owner = tab[label].owner;
+    const long long k = (long long)a.sc.start[*owner] + b;  // rank among the batch's new blocks
+    if (k < fresh) return (int32_t)(old + k);
+    return k - fresh < nv ? a.ev.victims[k - fresh] : -1;
 }
 
 __global__ __launch_bounds__(kThreads) void k_publish(InsertArgs a) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
-    if (r >= a.bat.R) return;
+    const WaveOf v = wave_of(a.bat);
+    if (a.ev.on && a.ix.state->ev_rebuild) reenter_survivors(a);
+    if (!v.any) return;
     const int bt = a.ix.block_tokens;
-    const int64_t maxb = a.bat.max_blocks;
-    int64_t o0;
-    const int32_t n = n_blocks(a.bat, r, bt, &o0);
-    const int32_t m0 = a.sc.m0[r];
-    const BatchEntry* __restrict__ tab = reinterpret_cast<const BatchEntry*>(a.sc.table);
+    const int64_t maxb = a.bat.max_blocks, r = v.r;
+    const int32_t b = v.b, m0 = a.sc.m0[r], n = a.sc.nblk[r];
     const HashTables* __restrict__ ht = a.ix.ht;
     int32_t* __restrict__ row = a.ids + r * maxb;
     uint8_t* __restrict__ crow = a.created + r * maxb;
-    for (int32_t b = lane; b < maxb; b += kWave)
-        if (b < m0 || b >= n) crow[b] = 0;
-    int32_t carry = m0 == 0 ? -1 : row[m0 - 1];  // id of the block before the window
-    int32_t m = n;                               // resident blocks after the call
+    if (b < maxb && (b < m0 || b >= n)) crow[b] = 0;
+    if (m0 == n && b == 0) a.m_out[r] = n;
+    const uint64_t clock = a.ev.on ? a.ix.state->clock : 0;
+    const long long old = (long long)a.ix.state->insert_old_count;
+    const long long fresh = a.tgt.capacity - old;                     // never-used ids
+    const long long nv = a.ev.on ? (long long)a.ix.state->ev_nv : 0;  // freed ids
     unsigned long long cas = 0, fails = 0, tombs_taken = 0;
-    for (int32_t w0 = m0; w0 < n; w0 += kWave) {
-        const int32_t b = w0 + lane;
-        const bool valid = b < n;
-        BatchEntry e;
-        e.node_id = -1;
-        e.owner = -1;
-        if (valid) e = tab[a.sc.label[r * maxb + b]];
-        const unsigned long long refused = ballot64(valid && e.node_id < 0);
-        if (refused) {
-            const int32_t cut = w0 + __ffsll((long long)refused) - 1;
-            m = cut < m ? cut : m;
-        }
-        int32_t parent = __shfl_up(e.node_id, 1, kWave);
-        if (lane == 0) parent = carry;
-        carry = __shfl(e.node_id, kWave - 1, kWave);
-        if (!valid) continue;
-        if (b >= m) {
-            row[b] = -1;
-            crow[b] = 0;
-            continue;
-        }
-        const int32_t id = e.node_id;
+    const bool is_new = b >= m0 && b < n;
+    int32_t id = -1, owner = -1;
+    if (is_new) id = new_id(a, a.sc.label[r * maxb + b], b, old, fresh, nv, &owner);
+    else if (a.ev.on && b < m0) id = row[b];
+    int32_t parent = __shfl_up(id, 1, kWave);
+    if (is_new) {
+        int32_t po;
+        if (b == m0)
+            parent = m0 == 0 ? -1 : row[m0 - 1];
+        else if (v.lane == 0)
+            parent = new_id(a, a.sc.label[r * maxb + b - 1], b - 1, old, fresh, nv, &po);
+        // refusals are a suffix of the request: one lane holds the cut
+        if (id < 0 && (b == m0 || parent >= 0)) a.m_out[r] = b;
+        if (id >= 0 && b == n - 1) a.m_out[r] = n;
+        const bool mine = id >= 0 && owner == (int32_t)r;
         row[b] = id;
-        const bool mine = e.owner == (int32_t)r;
         crow[b] = mine ? 1 : 0;
-        if (!mine) continue;
-        a.tgt.parent[id] = parent;
-        const int32_t* src = a.bat.tokens + o0 + (int64_t)b * bt;
-        int32_t* dst = a.tgt.tokens + (int64_t)id * bt;
-        for (int i = 0; i < bt; ++i) dst[i] = src[i];
-        const uint64_t ik = index_key(a.sc.keys[r * maxb + b], *ht);
-        uint64_t pos = slot_of(ik, ht->slot_seed, a.ix.slot_mask);
-        Slot* slots = a.tgt.slots;
-        // at most half the slots hold blocks and at most a quarter are
-        // deleted, so a free slot is always found
-        for (uint64_t step = 0; step <= a.ix.slot_mask; ++step) {
-            unsigned long long* kp = reinterpret_cast<unsigned long long*>(&slots[pos].key);
-            unsigned long long prev = atomicCAS(kp, kEmptyKey, (unsigned long long)ik);
-            ++cas;
-            bool got = prev == kEmptyKey;
-            if (!got && a.ev.on && prev == kTombKey) {
-                prev = atomicCAS(kp, kTombKey, (unsigned long long)ik);
+        if (mine) {
+            a.tgt.parent[id] = parent;
+            copy_tokens(a.tgt.tokens + (int64_t)id * bt, a.bat.tokens + a.bat.offsets[r] + (int64_t)b * bt, bt);
+            const uint64_t ik = index_key(a.sc.keys[r * maxb + b], *ht);
+            uint64_t pos = slot_of(ik, ht->slot_seed, a.ix.slot_mask);
+            Slot* slots = a.tgt.slots;
+            // at most half the slots hold blocks and at most a quarter are
+            // deleted, so a free slot is always found
+            for (uint64_t step = 0; step <= a.ix.slot_mask; ++step) {
+                unsigned long long* kp = reinterpret_cast<unsigned long long*>(&slots[pos].key);
+                unsigned long long prev = atomicCAS(kp, kEmptyKey, (unsigned long long)ik);
                 ++cas;
-                got = prev == kTombKey;
-                tombs_taken += got ? 1 : 0;
+                bool got = prev == kEmptyKey;
+                if (!got && a.ev.on && prev == kTombKey) {
+                    prev = atomicCAS(kp, kTombKey, (unsigned long long)ik);
+                    ++cas;
+                    got = prev == kTombKey;
+                    tombs_taken += got ? 1 : 0;
+                }
+                if (got) {
+                    slots[pos].id = id;
+                    slots[pos].parent = parent;
+                    break;
+                }
+                ++fails;
+                pos = (pos + 1) & a.ix.slot_mask;
             }
-            if (got) {
-                slots[pos].id = id;
-                slots[pos].parent = parent;
-                break;
+            if (a.ev.on) {
+                a.ev.depth[id] = b;
+                a.ev.prot[id] = 0;
+                a.ev.nkey[id] = ik;
+                a.ev.spos[id] = (uint32_t)pos;
             }
-            ++fails;
-            pos = (pos + 1) & a.ix.slot_mask;
-        }
-        if (a.ev.on) {  // (the rest was reset by assign, before any child counts itself here)
-            a.ev.nkey[id] = ik;
-            a.ev.spos[id] = (uint32_t)pos;
-            if (parent >= 0) atomicAdd(&a.ev.live[parent], 1);
         }
     }
-    if (lane == 0) a.m_out[r] = m;
-    count_cas(a, cas, fails, lane);
-    if (a.ev.on) wave_sub(&a.ix.state->tombstones, tombs_taken, lane);
+    // every block of the resident path counts one access (an id that held no
+    // block had F = H = 0)
+    if (a.ev.on && id >= 0) {
+        const uint64_t f = atomicAdd((unsigned long long*)&a.ev.freq[id], 1ull) + 1ull;
+        atomicMax((unsigned long long*)&a.ev.prio[id], (unsigned long long)(clock + f));
+    }
+    count_cas(a, cas, fails, v.lane);
+    if (a.ev.on) wave_sub(&a.ix.state->tombstones, tombs_taken, v.lane);
 }
 
 }  // namespace
@@ -443,7 +503,7 @@ size_t insert_scratch_bytes(int32_t R, int32_t max_blocks, uint64_t* table_entri
     while (t < 2 * rb) t <<= 1;
     *table_entries = t;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    return up(rb * 8) + up((size_t)R * 4) + up(rb * 4) + up((size_t)R * 4) * 2 +
+    return up(rb * 8) + up((size_t)R * 4) + up(rb * 4) + up((size_t)R * 4) * 3 +
            up(t * sizeof(BatchEntry)) + 256;
 }
 
@@ -459,15 +519,24 @@ void insert_scratch_carve(void* base, int32_t R, int32_t max_blocks, InsertScrat
     p += up((size_t)R * 4);
     out->label = reinterpret_cast<int32_t*>(p);
     p += up(rb * 4);
+    out->nblk = reinterpret_cast<int32_t*>(p);
+    p += up((size_t)R * 4);
     out->cnt = reinterpret_cast<int32_t*>(p);
     p += up((size_t)R * 4);
-    out->base = reinterpret_cast<int32_t*>(p);
+    out->start = reinterpret_cast<int32_t*>(p);
     p += up((size_t)R * 4);
     out->table = p;
     out->table_mask = t - 1;
     p += up(t * sizeof(BatchEntry));
     out->collision = reinterpret_cast<unsigned int*>(p);
 }
+
+namespace {
+// Workgroups of a kernel with one wave per (request, window).
+unsigned window_grid(const Batch& b) {
+    return (unsigned)(((int64_t)b.R * windows(b.max_blocks) + kWaves - 1) / kWaves);
+}
+}  // namespace
 
 hipError_t launch_insert_match(const IndexView& ix, const InsertTarget& tgt, const EvictView& ev,
                                const Batch& b, const InsertScratch& sc, int32_t* m_out, int32_t* ids,
@@ -476,48 +545,30 @@ hipError_t launch_insert_match(const IndexView& ix, const InsertTarget& tgt, con
     IndexView quiet = ix;  // the insert's own match is not an access
     quiet.freq = nullptr;
     quiet.prio = nullptr;
-    if ((e = launch_lookup(quiet, b, sc.m0, ids, s)) != hipSuccess) return e;
-    if ((e = launch_hash_all(ix, b, sc.keys, s)) != hipSuccess) return e;
-    const uint64_t tn = sc.table_mask + 1;
-    const uint64_t cg = (tn + kThreads - 1) / kThreads;
-    const unsigned cgrid = (unsigned)(cg < 65536 ? cg : 65536);
-    BatchEntry* table = reinterpret_cast<BatchEntry*>(sc.table);
+    const InsertMatch im{sc.keys, sc.nblk, sc.cnt, sc.table, sc.table_mask + 1, sc.collision, ev.on};
+    if ((e = launch_match(quiet, b, sc.m0, ids, im, s)) != hipSuccess) return e;
     InsertArgs a{quiet, tgt, ev, b, sc, m_out, ids, created};
-    const unsigned wgrid = (unsigned)((b.R + kWaves - 1) / kWaves);      // wave per request
-    const unsigned tgrid = (unsigned)((b.R + kThreads - 1) / kThreads);  // thread per request
-    hipLaunchKernelGGL(k_table_clear, dim3(cgrid), dim3(kThreads), 0, s, table, tn, sc.collision, 0,
-                       ix.state, ev.on);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const unsigned wgrid = window_grid(b);
     hipLaunchKernelGGL(k_claim, dim3(wgrid), dim3(kThreads), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_verify, dim3(wgrid), dim3(kThreads), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_table_clear, dim3(cgrid), dim3(kThreads), 0, s, table, tn, sc.collision, 1,
-                       ix.state, 0);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_claim_exact, dim3(tgrid), dim3(kThreads), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_count, dim3(wgrid), dim3(kThreads), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, a);
+    if (ev.on && evicts_in_rank(tgt.capacity))
+        hipLaunchKernelGGL(k_rank<true>, dim3(1), dim3(kRankThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_rank<false>, dim3(1), dim3(kRankThreads), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_insert_commit(const IndexView& ix, const InsertTarget& tgt, const EvictView& ev,
                                 const Batch& b, const InsertScratch& sc, int32_t* m_out, int32_t* ids,
                                 uint8_t* created, hipStream_t s) {
-    hipError_t e;
     IndexView quiet = ix;
     quiet.freq = nullptr;
     quiet.prio = nullptr;
     InsertArgs a{quiet, tgt, ev, b, sc, m_out, ids, created};
-    const unsigned wgrid = (unsigned)((b.R + kWaves - 1) / kWaves);
-    hipLaunchKernelGGL(k_assign, dim3(wgrid), dim3(kThreads), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_publish, dim3(wgrid), dim3(kThreads), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (ev.on) return launch_touch_paths(quiet, ev, m_out, ids, b.R, b.max_blocks, s);
-    return hipSuccess;
+    hipLaunchKernelGGL(k_publish, dim3(window_grid(b)), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace ptsd

@@ -53,18 +53,15 @@ constexpr int kSelGroups = 256;
 // Per-block eviction state and the scratch of the victim selection
 // (allocated with the store when eviction is on).
 struct EvictView {
-    uint64_t* freq;     // [capacity] F
-    uint64_t* prio;     // [capacity] H
-    int32_t* live;      // [capacity] children that hold an id
+    uint64_t* freq;     // [capacity] F, 0 for an id that holds no block
+    uint64_t* prio;     // [capacity] H, likewise
     int32_t* prot;      // [capacity] last insert epoch (DevState::ev_epoch) whose batch
                         // matched the block
     int32_t* depth;     // [capacity] 0 for a child of the root
     uint64_t* nkey;     // [capacity] index key, to rebuild the index
     uint32_t* spos;     // [capacity] index slot, to delete the entry
     uint64_t* wmask;    // [words] victims of the running insert, one bit per id
-    uint32_t* wcnt;     // [words] victims per word
-    uint32_t* wbase;    // [words] exclusive scan of wcnt
-    int32_t* victims;   // [capacity] freed ids, ascending
+    int32_t* victims;   // [capacity] freed ids, ascending (before that, the search's list)
     uint32_t* hist;     // [kSelPasses][kSelBins] digit histograms
     uint64_t* part;     // [kSelGroups][8] per-workgroup partials of the range pass
     int64_t words;      // ceil(capacity / 64)
@@ -83,7 +80,19 @@ struct Batch {
 // lookup.hip
 hipError_t launch_lookup(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids,
                          hipStream_t s);
-hipError_t launch_hash_all(const IndexView& ix, const Batch& b, uint64_t* keys, hipStream_t s);
+// An insert's match: the lookup (not an access), and what the insert's later
+// kernels need of it.
+struct InsertMatch {
+    uint64_t* keys;           // [R][max_blocks] out: chained key of every whole block
+    int32_t* nblk;            // [R] out: blocks of each request (0 for a malformed one)
+    int32_t* cnt;             // [R] out: zeroed
+    void* table;              // table_n 16-byte batch entries, emptied
+    uint64_t table_n;
+    unsigned int* collision;  // lowered
+    int32_t ev_on;            // 1: advance the eviction epoch
+};
+hipError_t launch_match(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids,
+                        const InsertMatch& im, hipStream_t s);
 
 // copy.hip
 struct CopyPlan {
@@ -181,9 +190,10 @@ struct BatchEntry;  // defined in insert.hip
 struct InsertScratch {
     uint64_t* keys;       // [R][max_blocks]
     int32_t* m0;          // [R] match length before the insert
+    int32_t* nblk;        // [R] blocks of each request
     int32_t* label;       // [R][max_blocks] batch-table slot of each new block
-    int32_t* cnt;         // [R] blocks each request is the first to need
-    int32_t* base;        // [R] exclusive scan of cnt
+    int32_t* cnt;         // [R] blocks each request is the first to need (its last ones)
+    int32_t* start;       // [R] rank of its block b among the batch's new blocks is start + b
     void* table;          // batch table, table_mask + 1 entries of 16 bytes
     uint64_t table_mask;
     unsigned int* collision;  // set when the fast claim must be redone exactly
@@ -197,8 +207,8 @@ struct InsertTarget {
     int32_t* tokens;
     int64_t capacity;
 };
-// An insert is enqueued in three parts: match (lookup .. id scan), then,
-// with eviction on, launch_evict, then commit (assign, publish, accesses).
+// An insert is enqueued in three parts: match (lookup .. ranks), then, with
+// eviction on, launch_evict, then commit (publish and accesses).
 hipError_t launch_insert_match(const IndexView& ix, const InsertTarget& tgt, const EvictView& ev,
                                const Batch& b, const InsertScratch& sc, int32_t* m_out, int32_t* ids,
                                uint8_t* created, hipStream_t s);
@@ -207,12 +217,9 @@ hipError_t launch_insert_commit(const IndexView& ix, const InsertTarget& tgt, co
                                 uint8_t* created, hipStream_t s);
 
 // evict.hip: victim selection and index maintenance of an insert (between
-// its match and its commit), and the accesses of its resident paths (at the
-// end of its commit).
+// its match and its commit).
 hipError_t launch_evict(const IndexView& ix, const InsertTarget& tgt, const EvictView& ev,
                         hipStream_t s);
-hipError_t launch_touch_paths(const IndexView& ix, const EvictView& ev, const int32_t* m,
-                              const int32_t* ids, int32_t R, int32_t max_blocks, hipStream_t s);
 
 // evict.hip: make the replica slots hold the hot set of the host tier.
 hipError_t launch_replicate(const IndexView& ix, const EvictView& ev, const CopyPlan& p,

@@ -22,6 +22,10 @@
 // With eviction on, every matched block counts one access: its frequency F
 // grows by one and its priority becomes max(H, L + F), which is L + F for
 // the final F whatever order the atomics land in.
+//
+// An insert's match is the same walk (kInsert): it also writes every block's
+// chained key, going on to hash the windows past the first miss, and readies
+// the insert's work space (see insert.hip).
 #include "kernels.hpp"
 
 namespace ptsd {
@@ -255,11 +259,37 @@ __device__ inline int32_t request_blocks(const Batch& b, int64_t r, int bt, int 
     return (int32_t)(n < b.max_blocks ? n : b.max_blocks);
 }
 
-// TOUCH: count accesses (eviction on); a variant of its own so that the
+// What a walk does besides matching: variants of their own, so that the
 // plain lookup keeps its register count.
-template <int BT, bool TOUCH>
+enum Mode {
+    kPlain,   // nothing
+    kTouch,   // count accesses (eviction on)
+    kInsert,  // an insert's match: keys of every block, work space made ready
+};
+
+// An insert's work space before its claim: the batch table empty (every
+// workgroup clears its share; the stores are not waited for), the collision
+// flag down, and the eviction epoch advanced, so that a replayed capture
+// marks its own matches.
+__device__ inline void insert_setup(const InsertMatch& im, DevState* st) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *im.collision = 0;
+        if (im.ev_on) {  // protection marks are compared with it; 0 marks nothing
+            const unsigned long long e = st->ev_epoch + 1;
+            st->ev_epoch = e >= 0x7FFFFFFFull ? 1ull : e;
+        }
+    }
+    uint4* t = static_cast<uint4*>(im.table);  // {word, owner, depth}
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < im.table_n;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        t[i] = make_uint4((uint32_t)kEmptyKey, (uint32_t)(kEmptyKey >> 32), 0x7FFFFFFFu, 0xFFFFFFFFu);
+}
+
+template <int BT, Mode MODE>
 __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, int32_t* __restrict__ m_out,
-                                                     int32_t* __restrict__ ids_out) {
+                                                     int32_t* __restrict__ ids_out, InsertMatch im) {
+    constexpr bool TOUCH = MODE == kTouch;
+    if (MODE == kInsert) insert_setup(im, ix.state);
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t r = (int64_t)blockIdx.x * kWavesPerGroup + (threadIdx.x / kWave);
     if (r >= bat.R) return;  // uniform per wave
@@ -286,6 +316,7 @@ __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, in
         win.stage(seq, w0, n, bt);
         const uint64_t c = active ? win.hash(cc.content_seed, bt) : 0;
         const uint64_t k = window_chain(c, carry_key, cc, lane);
+        if (MODE == kInsert && active) im.keys[r * bat.max_blocks + b] = k;  // one window: see launch_lookup
         const uint64_t ik = index_key(k, cc);
         int32_t cpar = -2;
         uint64_t pos = 0;
@@ -326,7 +357,13 @@ __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, in
     }
     const int fill_from = w0 < n ? w0 : n;
     for (int b = fill_from + lane; b < bat.max_blocks; b += kWave) row[b] = -1;
-    if (lane == 0) m_out[r] = m;
+    if (lane == 0) {
+        m_out[r] = m;
+        if (MODE == kInsert) {
+            im.nblk[r] = n;
+            im.cnt[r] = 0;
+        }
+    }
     if (ix.counters) {
         CounterSlot* cs = counter_slot(ix.state);
         wave_count(&cs->probes, probes, lane);
@@ -344,10 +381,12 @@ __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, in
 // first failing position decides; only when it found the right tokens under
 // another parent (a key collision) does that lane probe on, and the round is
 // checked again.
-template <int BT, bool TOUCH, int W>
+template <int BT, Mode MODE, int W>
 __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch bat,
                                                            int32_t* __restrict__ m_out,
-                                                           int32_t* __restrict__ ids_out) {
+                                                           int32_t* __restrict__ ids_out, InsertMatch im) {
+    constexpr bool TOUCH = MODE == kTouch;
+    if (MODE == kInsert) insert_setup(im, ix.state);
     __shared__ uint64_t sh_off[W];   // each window's chain offset (zero carry)
     __shared__ int32_t sh_last[W];   // candidate of each window's last lane
     __shared__ int32_t sh_fail[W];   // first failing lane per window (kWave: none)
@@ -384,6 +423,7 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
         uint64_t carry = carry_key;
         for (int i = 0; i < wv; ++i) carry = addmod61(mulmod61(p64, carry), sh_off[i]);
         const uint64_t k = addmod61(mulmod61(cc.lane_pow, carry), sl);
+        if (MODE == kInsert && active) im.keys[r * bat.max_blocks + b] = k;
         const uint64_t ik = index_key(k, cc);
         int32_t cpar = -2;
         uint64_t pos = 0;
@@ -432,6 +472,7 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
         if (fail < W * kWave) {
             m = r0 + fail < n ? r0 + fail : n;
             r0 += W * kWave;
+            if (MODE == kInsert) carry_key = sh_klast;  // the last round's writes: a barrier ago
             break;
         }
         carry_key = sh_klast;
@@ -440,7 +481,31 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
     }
     const int fill_from = r0 < n ? r0 : n;
     for (int b = fill_from + (int)threadIdx.x; b < bat.max_blocks; b += W * kWave) row[b] = -1;
-    if (threadIdx.x == 0) m_out[r] = m;
+    if (threadIdx.x == 0) {
+        m_out[r] = m;
+        if (MODE == kInsert) {
+            im.nblk[r] = n;
+            im.cnt[r] = 0;
+        }
+    }
+    if (MODE == kInsert) {  // keys of the rounds past the miss: no probing
+        for (; r0 < n; r0 += W * kWave) {
+            const int b = r0 + wv * kWave + lane;
+            __syncthreads();  // the round before has read sh_off and sh_klast
+            if (r0 + wv * kWave < n) win.stage(seq, r0 + wv * kWave, n, bt);
+            const uint64_t c = b < n ? win.hash(cc.content_seed, bt) : 0;
+            const uint64_t sl = window_chain(c, 0, cc, lane);
+            if (lane == kWave - 1) sh_off[wv] = sl;
+            __syncthreads();
+            uint64_t carry = carry_key;
+            for (int i = 0; i < wv; ++i) carry = addmod61(mulmod61(p64, carry), sh_off[i]);
+            const uint64_t k = addmod61(mulmod61(cc.lane_pow, carry), sl);
+            if (b < n) im.keys[r * bat.max_blocks + b] = k;
+            if (wv == W - 1 && lane == kWave - 1) sh_klast = k;
+            __syncthreads();
+            carry_key = sh_klast;
+        }
+    }
     if (ix.counters) {
         CounterSlot* cs = counter_slot(ix.state);
         wave_count(&cs->probes, probes, lane);
@@ -448,96 +513,50 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
     }
 }
 
-// Chained keys of every whole block of every request (no probing).
-template <int BT>
-__global__ __launch_bounds__(kThreads) void k_hash_all(IndexView ix, Batch bat, uint64_t* __restrict__ keys) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t r = (int64_t)blockIdx.x * kWavesPerGroup + (threadIdx.x / kWave);
-    if (r >= bat.R) return;
-    const int bt = BT ? BT : ix.block_tokens;
-    const ChainConsts cc = chain_consts(ix.ht, lane);
-    int64_t o0;
-    // malformed requests were already counted by the lookup of the same batch
-    int64_t a = bat.offsets[r], e = bat.offsets[r + 1];
-    int32_t n = 0;
-    o0 = 0;
-    if (!(a < 0 || e < a || e > bat.n_tokens)) {
-        o0 = a;
-        int64_t nb = (e - a) / bt;
-        n = (int32_t)(nb < bat.max_blocks ? nb : bat.max_blocks);
-    }
-    const int32_t* __restrict__ seq = bat.tokens + o0;
-    __shared__ int4 sh_tok[BT == 16 ? kThreads * kQuads : 1];
-    typename WindowOf<BT>::type win;
-    win.init(sh_tok, threadIdx.x / kWave, lane);
-    uint64_t carry = cc.root_key;
-    for (int w0 = 0; w0 < n; w0 += kWave) {
-        const int b = w0 + lane;
-        win.stage(seq, w0, n, bt);
-        const uint64_t c = b < n ? win.hash(cc.content_seed, bt) : 0;
-        const uint64_t k = window_chain(c, carry, cc, lane);
-        if (b < n) keys[r * bat.max_blocks + b] = k;
-        carry = shfl_u64(k, kWave - 1);
-    }
-}
-
 }  // namespace
 
 namespace {
-template <int W>
-void launch_wide(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, hipStream_t s) {
+template <Mode MODE, int W>
+void launch_wide(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, const InsertMatch& im,
+                 hipStream_t s) {
     const dim3 grid((unsigned)b.R), block(W * kWave);
-    const bool touch = ix.freq != nullptr;
-    if (ix.block_tokens == 16) {
-        if (touch)
-            hipLaunchKernelGGL((k_lookup_wide<16, true, W>), grid, block, 0, s, ix, b, m, ids);
-        else
-            hipLaunchKernelGGL((k_lookup_wide<16, false, W>), grid, block, 0, s, ix, b, m, ids);
-    } else {
-        if (touch)
-            hipLaunchKernelGGL((k_lookup_wide<0, true, W>), grid, block, 0, s, ix, b, m, ids);
-        else
-            hipLaunchKernelGGL((k_lookup_wide<0, false, W>), grid, block, 0, s, ix, b, m, ids);
-    }
+    if (ix.block_tokens == 16)
+        hipLaunchKernelGGL((k_lookup_wide<16, MODE, W>), grid, block, 0, s, ix, b, m, ids, im);
+    else
+        hipLaunchKernelGGL((k_lookup_wide<0, MODE, W>), grid, block, 0, s, ix, b, m, ids, im);
 }
 
-}  // namespace
-
-hipError_t launch_lookup(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, hipStream_t s) {
+template <Mode MODE>
+hipError_t launch(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, const InsertMatch& im,
+                  hipStream_t s) {
     // requests of more than one window: a workgroup per request, windows in
     // parallel (4 waves up to 256 blocks, 8 up to 512, 16 beyond)
     if (b.max_blocks > kWave) {
         if (b.max_blocks <= 4 * kWave)
-            launch_wide<4>(ix, b, m, ids, s);
+            launch_wide<MODE, 4>(ix, b, m, ids, im, s);
         else if (b.max_blocks <= 8 * kWave)
-            launch_wide<8>(ix, b, m, ids, s);
+            launch_wide<MODE, 8>(ix, b, m, ids, im, s);
         else
-            launch_wide<16>(ix, b, m, ids, s);
+            launch_wide<MODE, 16>(ix, b, m, ids, im, s);
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)((b.R + kWavesPerGroup - 1) / kWavesPerGroup);
-    const bool touch = ix.freq != nullptr;
-    if (ix.block_tokens == 16) {
-        if (touch)
-            hipLaunchKernelGGL((k_lookup<16, true>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids);
-        else
-            hipLaunchKernelGGL((k_lookup<16, false>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids);
-    } else {
-        if (touch)
-            hipLaunchKernelGGL((k_lookup<0, true>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids);
-        else
-            hipLaunchKernelGGL((k_lookup<0, false>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids);
-    }
+    if (ix.block_tokens == 16)
+        hipLaunchKernelGGL((k_lookup<16, MODE>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids, im);
+    else
+        hipLaunchKernelGGL((k_lookup<0, MODE>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids, im);
     return hipGetLastError();
 }
+}  // namespace
 
-hipError_t launch_hash_all(const IndexView& ix, const Batch& b, uint64_t* keys, hipStream_t s) {
-    const unsigned grid = (unsigned)((b.R + kWavesPerGroup - 1) / kWavesPerGroup);
-    if (ix.block_tokens == 16)
-        hipLaunchKernelGGL(k_hash_all<16>, dim3(grid), dim3(kThreads), 0, s, ix, b, keys);
-    else
-        hipLaunchKernelGGL(k_hash_all<0>, dim3(grid), dim3(kThreads), 0, s, ix, b, keys);
-    return hipGetLastError();
+hipError_t launch_lookup(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, hipStream_t s) {
+    const InsertMatch none{};
+    return ix.freq ? launch<kTouch>(ix, b, m, ids, none, s) : launch<kPlain>(ix, b, m, ids, none, s);
+}
+
+hipError_t launch_match(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids,
+                        const InsertMatch& im, hipStream_t s) {
+    return launch<kInsert>(ix, b, m, ids, im, s);
 }
 
 }  // namespace ptsd

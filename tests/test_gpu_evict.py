@@ -162,3 +162,40 @@ def test_stream_evict_small():
     t.check_meta()
     assert t.gpu.stats()["evictions"] > 0
     t.close()
+
+
+@pytest.mark.parametrize("capacity,weak", [(1, 0), (64, 0), (65, 1), (1023, 0), (1025, 0), (16384, 0),
+                                           (16385, 0), (24000, 0)])
+def test_evicting_inserts_by_store_size(capacity, weak):
+    """Both ways of selecting victims (one workgroup up to 16,384 blocks, a grid above) on
+    each side of their edges, with requests of several 64-block windows, priorities more than
+    one 11-bit digit apart, ties in priority and depth, and an insert that evicts everything."""
+    rng = np.random.default_rng(capacity)
+    bt, maxb = 4, 150
+    flags = EVICT | ((P.PTSTORE_FLAG_WEAK_HASH | P.PTSTORE_FLAG_WEAK_TAGS) if weak else 0)
+    t = Twin(1, 1, 8, bt, capacity, flags=flags, payload=False)
+    kept = [rng.integers(0, 9, size=int(rng.integers(1, maxb)) * bt, dtype=np.int32) for _ in range(8)]
+
+    def batch(n_req, lo, hi):
+        seqs = []
+        for _ in range(n_req):
+            stem = kept[int(rng.integers(len(kept)))]
+            cut = int(rng.integers(0, len(stem) // bt + 1)) * bt
+            own = rng.integers(0, 50, size=int(rng.integers(lo, hi + 1)) * bt + int(rng.integers(0, bt)),
+                               dtype=np.int32)
+            seqs.append(np.concatenate([stem[:cut], own]))
+        return synth.concat_requests(seqs)
+
+    n_req = max(1, capacity // 64)
+    for _ in range(3):  # fill
+        t.insert(*batch(n_req, 1, 60), maxb)
+    t.lookup(*synth.concat_requests([kept[0][:2 * bt]] * 3000), maxb)  # far more accesses than the rest
+    for r, (lo, hi) in enumerate([(1, 1), (1, 6), (0, 40)]):
+        t.insert(*batch(max(1, n_req // 2), lo, hi), maxb)
+        t.lookup(*batch(5, 0, 2), maxb)
+        t.check_evict()
+    t.insert(*batch(n_req * 4, 30, 60), maxb)  # more new blocks than can be freed
+    t.check_evict()
+    t.check_meta()
+    assert t.gpu.stats()["evictions"] > 0
+    t.close()
