@@ -111,3 +111,51 @@ def test_random_sizes_against_the_oracle(seed):
     if evict:
         t.check_evict()
     t.close()
+
+
+@pytest.mark.parametrize("R,maxb,dim,cpg,skew", [
+    (1, 1, 4, 0, 0), (1, 63, 4, 0, 0), (3, 65, 4, 3, 1), (64, 128, 8, 0, 0), (130, 45, 4096, 0, 0),
+    (5, 40, 4100, 2, 3), (256, 256, 4, 0, 0), (257, 256, 4, 0, 0), (7, 9, 12000, 0, 0)])
+def test_scatter_of_any_flags(R, maxb, dim, cpg, skew):
+    """A scatter's list is built in one launch from up to 65,536 created flags, in three
+    beyond: flags at both ends of a 64-flag mask and of the limit, flags at addresses that are
+    not a multiple of 16, slabs of one 16-byte vector to several 32 KiB pieces, several slabs
+    per unit, holes and out-of-range entries, and a layer range."""
+    rng = np.random.default_rng(R * 100 + maxb)
+    E = R * maxb
+    cap = min(E, 700)
+    t = Twin(3, 1, dim, 2, cap)
+    chain = np.arange(2 * cap, dtype=np.int32)
+    (m, _, _), _ = t.insert(chain, np.array([0, 2 * cap], dtype=np.int64), cap)
+    if cpg:
+        t.gpu.set_copy_shape(chunks_per_group=cpg)
+    created = np.zeros(E, dtype=np.uint8)
+    on = rng.permutation(E)[:cap]
+    if E > 64:
+        on[:2] = (0, E - 1) if 0 not in on[2:] and E - 1 not in on[2:] else on[:2]
+    created[on] = rng.integers(1, 256, size=cap, dtype=np.uint8)
+    ids = rng.integers(0, cap, size=E).astype(np.int32)
+    ids[on] = rng.permutation(cap)
+    NB = cap + 7
+    bt = np.full(E, -1, dtype=np.int32)
+    bt[on] = rng.permutation(NB)[:cap]
+    bt[on[::7]] = -1
+    bt[on[3::11]] = NB + 2
+    ids[on[5::13]] = cap + 1
+    from tests.twin import DEV, random_bytes, to_dev, host
+    flags = torch.zeros(E + 16, dtype=torch.uint8, device=DEV)[skew:skew + E]
+    flags.copy_(to_dev(created))
+    cache = random_bytes(NB * t.shape.block_bytes, 5)
+    pool = t.gpu.pool_tensor()
+    pool.zero_()
+    b0, r0 = t.gpu.stats()["bad_entries"], t.ref.bad_entries
+    shaped = (R, maxb)
+    t.ref.pool()[:] = 0
+    for layers in ((1, 2), None):
+        t.gpu.scatter(to_dev(ids.reshape(shaped)), flags.view(shaped), to_dev(bt.reshape(shaped)), cache,
+                      layers=layers)
+        t.ref.scatter(ids.reshape(shaped), created.reshape(shaped), bt.reshape(shaped), host(cache), NB,
+                      layers=layers)
+        t.check_pool()
+    assert t.gpu.stats()["bad_entries"] - b0 == t.ref.bad_entries - r0
+    t.close()
