@@ -145,6 +145,14 @@ __device__ inline uint64_t content_hash_mem(const int32_t* __restrict__ blk, int
     return content_hash_final(h);
 }
 
+// Four tokens of a request in one load. A request starts at any token, and
+// global loads of 16 bytes need 4-byte alignment only.
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline int4 load_tokens4(const int32_t* p) {
+    const v4i_any v = *reinterpret_cast<const v4i_any*>(p);
+    return make_int4(v.x, v.y, v.z, v.w);
+}
+
 // One index slot in one 16-byte load: a probe learns the key, the id and the
 // parent of a slot at once, with no second dependent load.
 __device__ inline Slot load_slot(const Slot* p) {

@@ -73,25 +73,18 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr uint32_t kStoreLabel = 0x80000000u;  // parent label of a stored block: bit 31 | (id + 1)
 
-// A block's tokens move four at a time where all addresses allow it (block
-// sizes that are multiples of 4, requests that start on 16 bytes), sixteen
-// in flight: a token per step, each waiting for the one before, had been
-// half of publish.
-__device__ inline bool by_fours(const int32_t* a, const int32_t* b, int bt) {
-    return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0 && (bt & 3) == 0;
-}
-
+// A block's tokens move four at a time where the block size allows it
+// (stored rows then start on 16 bytes), sixteen in flight: a token per step,
+// each waiting for the one before, had been half of publish.
 __device__ inline bool same_tokens(const int32_t* __restrict__ a, const int32_t* __restrict__ b, int bt) {
-    if (by_fours(a, b, bt)) {
-        const int4* x = reinterpret_cast<const int4*>(a);
-        const int4* y = reinterpret_cast<const int4*>(b);
+    if ((bt & 3) == 0) {
         bool eq = true;
         for (int i = 0; i < bt / 4; i += 4) {
             int4 u[4], w[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {  // past the end: the last piece again
-                u[j] = x[min(i + j, bt / 4 - 1)];
-                w[j] = y[min(i + j, bt / 4 - 1)];
+                u[j] = load_tokens4(a + 4 * min(i + j, bt / 4 - 1));
+                w[j] = load_tokens4(b + 4 * min(i + j, bt / 4 - 1));
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -104,12 +97,13 @@ __device__ inline bool same_tokens(const int32_t* __restrict__ a, const int32_t*
     return true;
 }
 
+// dst: a stored row
 __device__ inline void copy_tokens(int32_t* __restrict__ dst, const int32_t* __restrict__ src, int bt) {
-    if (by_fours(dst, src, bt)) {
+    if ((bt & 3) == 0) {
         for (int i = 0; i < bt / 4; i += 4) {
             int4 u[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) u[j] = reinterpret_cast<const int4*>(src)[min(i + j, bt / 4 - 1)];
+            for (int j = 0; j < 4; ++j) u[j] = load_tokens4(src + 4 * min(i + j, bt / 4 - 1));
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (i + j < bt / 4) reinterpret_cast<int4*>(dst)[i + j] = u[j];
