@@ -722,15 +722,24 @@ int ptstore_gather_layers(ptstore_t* s, const int32_t* ids, const int32_t* m,
     if (dev.rc) return dev.rc;
     int rc = PTSTORE_OK;
     hipStream_t st = (hipStream_t)stream;
+    const CopyPlan plan = range_plan(s, layer_begin, layer_end);
+    hipError_t e;
+    // made and checked whether or not this call uses it, so that what a later
+    // call finds does not depend on the route of this one
     void* scr = nullptr;
     uint64_t tcap = 0;
     ptstore::StreamScratch* ent = nullptr;
     rc = copy_scratch_for(s, st, R, max_blocks, &scr, &tcap, &ent, "ptstore_gather: scratch");
     if (rc) return rc;
+    if (gathers_without_list(plan, R)) {
+        { Timed t(s, 4, st); }  // a selection of no kernels
+        Timed t(s, 0, st);
+        e = launch_gather_one(plan, ids, m, block_table, max_blocks, static_cast<uint8_t*>(cache),
+                              cache_blocks, layer_begin, layer_end, st);
+        return e == hipSuccess ? PTSTORE_OK : fail(PTSTORE_ERR_HIP, "ptstore_gather: launch", e);
+    }
     CopyScratch sc;
     copy_scratch_carve(scr, R, max_blocks, tcap, &sc);
-    const CopyPlan plan = range_plan(s, layer_begin, layer_end);
-    hipError_t e;
     {
         Timed t(s, 4, st);
         e = launch_gather_select(plan, sc, ids, m, block_table, R, max_blocks, cache_blocks, st);
@@ -854,6 +863,12 @@ int ptstore_lookup_gather_noalloc(ptstore_t* s, const int32_t* tokens, const int
     CopyScratch sc;
     copy_scratch_carve(sp, R, max_blocks, kNoAllocTableSlots, &sc);
     const CopyPlan plan = copy_plan(s);
+    if (e == hipSuccess && gathers_without_list(plan, R)) {
+        e = launch_gather_one(plan, ids, m, block_table, max_blocks, static_cast<uint8_t*>(cache),
+                              cache_blocks, 0, s->cfg.num_layers, st);
+        return e == hipSuccess ? PTSTORE_OK
+                               : fail(PTSTORE_ERR_HIP, "ptstore_lookup_gather_noalloc: launch", e);
+    }
     if (e == hipSuccess) {
         e = launch_gather_select(plan, sc, ids, m, block_table, R, max_blocks, cache_blocks, st);
         if (e != hipSuccess) static_dirty(s->device, true, true);

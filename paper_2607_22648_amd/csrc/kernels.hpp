@@ -178,6 +178,14 @@ hipError_t launch_scatter_select(const CopyPlan& p, const CopyScratch& sc, const
 hipError_t launch_gather_copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache,
                               int64_t cache_blocks, int32_t R, int32_t max_blocks, int32_t l0,
                               int32_t l1, hipStream_t s);
+// A gather of one request into device rows without a list: select and copy in
+// one launch, for a call that does not keep its list (no host tier only).
+inline bool gathers_without_list(const CopyPlan& p, int32_t R) {
+    return R == 1 && p.tier.host_blocks == 0;
+}
+hipError_t launch_gather_one(const CopyPlan& p, const int32_t* ids, const int32_t* m,
+                             const int32_t* block_table, int32_t max_blocks, uint8_t* cache,
+                             int64_t cache_blocks, int32_t l0, int32_t l1, hipStream_t s);
 hipError_t launch_scatter_copy(const CopyPlan& p, const CopyScratch& sc, const uint8_t* cache,
                                int64_t cache_blocks, int32_t R, int32_t max_blocks, int32_t l0,
                                int32_t l1, hipStream_t s);

@@ -1,0 +1,47 @@
+"""A gather of one request copies from the request's own entries, without a block list. Against
+the CPU oracle, bit-exact."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from tests.twin import Twin, DEV, host, to_dev
+
+
+@pytest.mark.parametrize("m", [0, 1, 40, 90, 130, -3])
+@pytest.mark.parametrize("slabs", [None, (64, 4096, 16, 32768, 200 * 16)])
+def test_one_request_of_any_entries(slabs, m):
+    """Match lengths below zero, inside and past the entries, holes, ids and cache blocks out of
+    range, repeated ids, more units than workgroups, layer ranges."""
+    rng = np.random.default_rng(7 + m)
+    maxb, cap = 130, 60
+    t = Twin(5, 1, 64, 2, cap, layer_chunk_bytes=slabs)
+    chain = np.arange(2 * cap, dtype=np.int32)
+    t.insert(chain, np.array([0, 2 * cap], dtype=np.int64), cap)
+    pool = t.gpu.pool_tensor()
+    pool.copy_(torch.randint(0, 256, pool.shape, dtype=torch.uint8, device=DEV))
+    t.ref.pool()[:] = host(pool).reshape(t.ref.pool().shape)
+    NB = maxb + 5
+    ids = rng.integers(0, cap, size=(1, maxb)).astype(np.int32)
+    bt = rng.permutation(NB)[:maxb].astype(np.int32).reshape(1, maxb)
+    bt[0, 3::7] = -1
+    bt[0, 5::17] = NB + 4
+    ids[0, 8::19] = -1
+    ids[0, 9::23] = cap
+    ms = np.array([m], dtype=np.int32)
+    for grid, layers in ((0, None), (3, None), (0, (1, 4))):
+        if grid:
+            t.gpu.set_copy_shape(grid=grid)
+        b0, r0 = t.gpu.stats()["bad_entries"], t.ref.bad_entries
+        dst = torch.full((NB * t.shape.block_bytes,), 0x5A, dtype=torch.uint8, device=DEV)
+        t.gpu.gather(to_dev(ids), to_dev(ms), to_dev(bt), dst, layers=layers)
+        ref = np.full(dst.numel(), 0x5A, dtype=np.uint8)
+        t.ref.gather(ids, ms, bt, ref, NB, layers=layers)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(dst), ref)
+        assert t.gpu.stats()["bad_entries"] - b0 == t.ref.bad_entries - r0
+    t.close()
