@@ -756,8 +756,10 @@ struct CopyArgs {
     const int32_t* m;        // how many of them are moved
     DevState* state;         // where entries out of range are counted
     int64_t entries;         // (request, block) slots
-    const unsigned long long* first;  // the first descriptor (null: 0)
-    const unsigned long long* total;  // descriptors from there
+    const unsigned long long* total;    // descriptors of device rows, from 0
+    const unsigned long long* first_h;  // the first descriptor of a host-tier row
+    const unsigned long long* total_h;  // descriptors from there
+    int32_t host_wgs;                   // workgroups that copy host-tier rows (0: no host tier)
     int64_t block_bytes;
     int64_t chunk_bytes;
     int64_t cache_blocks;
@@ -767,6 +769,32 @@ struct CopyArgs {
     int32_t c_lo, c_hi;        // chunks moved: 2*l0 .. 2*l1-1
     const int64_t* lbase;      // per-layer slab bases (null when uniform)
 };
+
+// A workgroup's part of the call. With a host tier the first host_wgs
+// workgroups walk the descriptors of host-tier rows, which the host link
+// bounds, and all others those of device rows at the same time: one after
+// the other, in two launches, the device rows' copy had come on top (a
+// request pair of which 72 of 960 blocks of 5 MiB lie in host memory: 8.40
+// ms in two launches, 6.70 in one).
+struct Share {
+    unsigned long long first, total;  // descriptors
+    unsigned long long wg, wgs;       // this workgroup among those of the part
+};
+__device__ inline Share share_of(const CopyArgs& a) {
+    Share h;
+    if ((int)blockIdx.x < a.host_wgs) {
+        h.first = *a.first_h;
+        h.total = *a.total_h;
+        h.wg = blockIdx.x;
+        h.wgs = (unsigned)a.host_wgs;
+    } else {
+        h.first = 0;
+        h.total = *a.total;
+        h.wg = blockIdx.x - (unsigned)a.host_wgs;
+        h.wgs = gridDim.x - (unsigned)a.host_wgs;
+    }
+    return h;
+}
 
 // Unit number -> descriptor. Nearly every call has fewer than 2^32 possible
 // units; a 64-bit division is several times as long.
@@ -784,10 +812,11 @@ __device__ inline unsigned long long unit_desc(unsigned long long unit, int grou
 // are sparse, launches 16 times what the device holds, looping.
 // Scatter, uniform slabs: a unit is (pair, group of chunks_per_group slabs).
 __global__ __launch_bounds__(1024) void k_copy_pairs(CopyArgs a) {
-    const unsigned long long units = *a.total * (unsigned long long)a.groups;
-    const Pair* pairs = a.pairs + (a.first ? *a.first : 0ull);
+    const Share h = share_of(a);
+    const unsigned long long units = h.total * (unsigned long long)a.groups;
+    const Pair* pairs = a.pairs + h.first;
     const int n16 = (int)(a.chunk_bytes >> 4);
-    for (unsigned long long unit = blockIdx.x; unit < units; unit += gridDim.x) {
+    for (unsigned long long unit = h.wg; unit < units; unit += h.wgs) {
         const unsigned long long d = unit_desc(unit, a.groups);
         const int g = (int)(unit - d * (unsigned)a.groups);
         const Pair p = pairs[d];
@@ -827,15 +856,15 @@ __device__ inline int32_t slice_dests(const CopyArgs& a, const Slice& q) {
 // descriptors are the request's own entries, each checked here as the
 // selection would; a bad one is counted by its first unit. A lookup and
 // gather of 48 blocks of 128 KiB takes 15.8 us so, 19.5 with the selection's
-// launch between them; of 175 blocks of 4 MiB 143 instead of 150.
+// launch between them; of 175 blocks of 2 MiB 143 instead of 150.
 template <bool ENTRIES>
 __global__ __launch_bounds__(1024) void k_copy_slices(CopyArgs a) {
-    const unsigned long long first = !ENTRIES && a.first ? *a.first : 0ull;
-    const unsigned long long units = (ENTRIES ? (unsigned long long)a.entries : *a.total) *
+    const Share h = ENTRIES ? Share{0, 0, blockIdx.x, gridDim.x} : share_of(a);
+    const unsigned long long units = (ENTRIES ? (unsigned long long)a.entries : h.total) *
                                      (unsigned long long)a.groups;
     const int n16 = (int)(a.chunk_bytes >> 4);
     const int nt = blockDim.x;
-    for (unsigned long long unit = blockIdx.x; unit < units; unit += gridDim.x) {
+    for (unsigned long long unit = h.wg; unit < units; unit += h.wgs) {
         const unsigned long long d = unit_desc(unit, a.groups);
         const int g = (int)(unit - d * (unsigned)a.groups);
         Slice q;
@@ -854,7 +883,7 @@ __global__ __launch_bounds__(1024) void k_copy_slices(CopyArgs a) {
             q.n = 1;
             lane_cb = cb;
         } else {
-            q = a.slices[first + d];
+            q = a.slices[h.first + d];
             lane_cb = slice_dests(a, q);
         }
         const int c0 = a.c_lo + g * a.chunks_per_group;
@@ -925,17 +954,17 @@ template <bool GATHER, bool ENTRIES>
 __global__ __launch_bounds__(1024) void k_copy_spans(CopyArgs a) {
     __shared__ int64_t lb[kMaxVarLayers + 1];
     const unsigned long long spans = (unsigned)a.groups;  // kSpanBytes units per descriptor
-    const unsigned long long total = ENTRIES ? (unsigned long long)max(min((int64_t)*a.m, a.entries), (int64_t)0)
-                                             : *a.total;
-    const unsigned long long units = total * spans;
-    const unsigned long long first = a.first ? *a.first : 0ull;
-    if (blockIdx.x >= units) return;  // the whole workgroup: nothing to move
+    const Share h = ENTRIES ? Share{0, (unsigned long long)max(min((int64_t)*a.m, a.entries), (int64_t)0),
+                                    blockIdx.x, gridDim.x}
+                            : share_of(a);
+    const unsigned long long units = h.total * spans, first = h.first;
+    if (h.wg >= units) return;  // the whole workgroup: nothing to move
     const int l0 = a.c_lo >> 1, l1 = a.c_hi >> 1, nl = l1 - l0;
     for (int l = l0 + (int)threadIdx.x; l <= l1; l += blockDim.x) lb[l - l0] = a.lbase[l];
     __syncthreads();
     const int64_t b0 = lb[0], b1 = lb[nl];
     const int64_t step = 16 * (int64_t)blockDim.x;
-    for (unsigned long long unit = blockIdx.x; unit < units; unit += gridDim.x) {
+    for (unsigned long long unit = h.wg; unit < units; unit += h.wgs) {
         const unsigned long long d = unit_desc(unit, a.groups);
         const int64_t s0 = b0 + (int64_t)(unit - d * spans) * kSpanBytes;
         const int64_t s1 = min(s0 + (int64_t)kSpanBytes, b1);
@@ -1083,9 +1112,12 @@ CopyArgs copy_args(const CopyPlan& p, uint8_t* cache, int64_t cache_blocks, int3
     return a;
 }
 
+// Most workgroups of a launch, by its work-items.
+int64_t work_item_limit(int32_t threads) { return (1ll << 31) / threads; }
+
 // Workgroups of a copy of at most `bound` units.
-int64_t copy_grid(const CopyPlan& p, bool gather, int64_t bound) {
-    const int64_t cap = (1ll << 31) / p.threads;  // launch limit on work-items
+int64_t copy_grid(const CopyPlan& p, bool gather, int32_t threads, int64_t bound) {
+    const int64_t cap = work_item_limit(threads);
     int64_t grid = p.grid ? p.grid : (gather ? (int64_t)p.gather_grid : (int64_t)p.loop_grid);
     if (grid > bound) grid = bound;
     return grid < cap ? grid : cap;
@@ -1101,32 +1133,25 @@ hipError_t copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache, int64_
     a.total = GATHER ? sc.nslices : sc.total;  // a gather has at most one slice per entry
     a.entries = (int64_t)R * max_blocks;
     const int64_t bound = a.entries * a.groups;  // units if every entry moves
-    const int64_t cap = (1ll << 31) / p.threads;  // launch limit on work-items
-    const int64_t grid = copy_grid(p, GATHER, bound);
+    const int32_t threads = p.threads;
+    int64_t grid = copy_grid(p, GATHER, threads, bound);
     if (grid < 1) return hipSuccess;
+    if (p.tier.host_blocks > 0) {
+        // a small looping grid for the host link, whose workgroups start
+        // first; the device's other compute units stay free for device rows
+        // (of this call or of calls on other streams)
+        a.first_h = sc.total;
+        a.total_h = GATHER ? sc.nslices_h : sc.total_h;
+        a.host_wgs = (int32_t)(bound < p.host_grid ? bound : p.host_grid);
+        const int64_t room = work_item_limit(threads) - a.host_wgs;
+        grid = (grid < room ? grid : room) + a.host_wgs;
+    }
     if (p.lbase)
-        hipLaunchKernelGGL((k_copy_spans<GATHER, false>), dim3((unsigned)grid), dim3(p.threads), 0, s, a);
+        hipLaunchKernelGGL((k_copy_spans<GATHER, false>), dim3((unsigned)grid), dim3(threads), 0, s, a);
     else if (GATHER)
-        hipLaunchKernelGGL(k_copy_slices<false>, dim3((unsigned)grid), dim3(p.threads), 0, s, a);
+        hipLaunchKernelGGL(k_copy_slices<false>, dim3((unsigned)grid), dim3(threads), 0, s, a);
     else
-        hipLaunchKernelGGL(k_copy_pairs, dim3((unsigned)grid), dim3(p.threads), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.tier.host_blocks == 0) return e;
-    // host-tier rows: bound by the host link, so a small looping grid moves
-    // them and the device's other compute units stay free for device rows
-    // (of this call or of calls on other streams)
-    CopyArgs h = a;
-    h.first = sc.total;
-    h.total = GATHER ? sc.nslices_h : sc.total_h;
-    int64_t hg = p.host_grid;
-    if (hg > bound) hg = bound;
-    if (hg > cap) hg = cap;
-    if (p.lbase)
-        hipLaunchKernelGGL((k_copy_spans<GATHER, false>), dim3((unsigned)hg), dim3(p.threads), 0, s, h);
-    else if (GATHER)
-        hipLaunchKernelGGL(k_copy_slices<false>, dim3((unsigned)hg), dim3(p.threads), 0, s, h);
-    else
-        hipLaunchKernelGGL(k_copy_pairs, dim3((unsigned)hg), dim3(p.threads), 0, s, h);
+        hipLaunchKernelGGL(k_copy_pairs, dim3((unsigned)grid), dim3(threads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1240,7 +1265,7 @@ hipError_t launch_gather_one(const CopyPlan& p, const int32_t* ids, const int32_
     a.m = m;
     a.state = p.state;
     a.entries = max_blocks;
-    const int64_t grid = copy_grid(p, true, a.entries * a.groups);
+    const int64_t grid = copy_grid(p, true, p.threads, a.entries * a.groups);
     if (grid < 1) return hipSuccess;
     if (p.lbase)
         hipLaunchKernelGGL((k_copy_spans<true, true>), dim3((unsigned)grid), dim3(p.threads), 0, s, a);
