@@ -16,8 +16,8 @@
 // link.
 //
 // A gather of one request from device rows copies straight from the request's
-// entries (k_copy_slices<true>, k_copy_spans<true, true>). Any other call runs
-// in two parts, like the paper's bulk transfer of a list of (offset, size)
+// entries (k_copy_entries, k_copy_entry_spans). Any other call runs in two
+// parts, like the paper's bulk transfer of a list of (offset, size)
 // segments in one request (Section 4.1, RDMA-aware consolidation):
 //   select  count the blocks each request must move (wave per request), scan
 //           the counts, then write a dense list of (row, cache block)
@@ -858,7 +858,7 @@ __device__ inline int32_t slice_dests(const CopyArgs& a, const Slice& q) {
 // gather of 48 blocks of 128 KiB takes 15.8 us so, 19.5 with the selection's
 // launch between them; of 175 blocks of 2 MiB 143 instead of 150.
 template <bool ENTRIES>
-__global__ __launch_bounds__(1024) void k_copy_slices(CopyArgs a) {
+__device__ inline void copy_slices(const CopyArgs& a) {
     const Share h = ENTRIES ? Share{0, 0, blockIdx.x, gridDim.x} : share_of(a);
     const unsigned long long units = (ENTRIES ? (unsigned long long)a.entries : h.total) *
                                      (unsigned long long)a.groups;
@@ -914,6 +914,9 @@ __global__ __launch_bounds__(1024) void k_copy_slices(CopyArgs a) {
     }
 }
 
+__global__ __launch_bounds__(1024) void k_copy_slices(CopyArgs a) { copy_slices<false>(a); }
+__global__ __launch_bounds__(1024) void k_copy_entries(CopyArgs a) { copy_slices<true>(a); }
+
 // Per-layer slab sizes. Layers l0 .. l1-1 of a pool row are one contiguous
 // byte range [lbase[l0], lbase[l1]); a unit is (descriptor, kSpanBytes of
 // that range), so every workgroup moves the same amount however small the
@@ -951,7 +954,7 @@ __device__ inline v4u* span_cache(const CopyArgs& a, const int64_t* lb, int li, 
 // and written to each of the slice's cache blocks; a scatter's is (pair,
 // span).
 template <bool GATHER, bool ENTRIES>
-__global__ __launch_bounds__(1024) void k_copy_spans(CopyArgs a) {
+__device__ inline void copy_spans(const CopyArgs& a) {
     __shared__ int64_t lb[kMaxVarLayers + 1];
     const unsigned long long spans = (unsigned)a.groups;  // kSpanBytes units per descriptor
     const Share h = ENTRIES ? Share{0, (unsigned long long)max(min((int64_t)*a.m, a.entries), (int64_t)0),
@@ -1024,6 +1027,12 @@ __global__ __launch_bounds__(1024) void k_copy_spans(CopyArgs a) {
         }
     }
 }
+
+template <bool GATHER>
+__global__ __launch_bounds__(1024) void k_copy_spans(CopyArgs a) {
+    copy_spans<GATHER, false>(a);
+}
+__global__ __launch_bounds__(1024) void k_copy_entry_spans(CopyArgs a) { copy_spans<true, true>(a); }
 
 // Whole blocks from one row to another (replication): pairs[k].row is the
 // source row, pairs[k].cb the destination row; *total pairs. A block is
@@ -1147,9 +1156,9 @@ hipError_t copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache, int64_
         grid = (grid < room ? grid : room) + a.host_wgs;
     }
     if (p.lbase)
-        hipLaunchKernelGGL((k_copy_spans<GATHER, false>), dim3((unsigned)grid), dim3(threads), 0, s, a);
+        hipLaunchKernelGGL(k_copy_spans<GATHER>, dim3((unsigned)grid), dim3(threads), 0, s, a);
     else if (GATHER)
-        hipLaunchKernelGGL(k_copy_slices<false>, dim3((unsigned)grid), dim3(threads), 0, s, a);
+        hipLaunchKernelGGL(k_copy_slices, dim3((unsigned)grid), dim3(threads), 0, s, a);
     else
         hipLaunchKernelGGL(k_copy_pairs, dim3((unsigned)grid), dim3(threads), 0, s, a);
     return hipGetLastError();
@@ -1268,9 +1277,9 @@ hipError_t launch_gather_one(const CopyPlan& p, const int32_t* ids, const int32_
     const int64_t grid = copy_grid(p, true, p.threads, a.entries * a.groups);
     if (grid < 1) return hipSuccess;
     if (p.lbase)
-        hipLaunchKernelGGL((k_copy_spans<true, true>), dim3((unsigned)grid), dim3(p.threads), 0, s, a);
+        hipLaunchKernelGGL(k_copy_entry_spans, dim3((unsigned)grid), dim3(p.threads), 0, s, a);
     else
-        hipLaunchKernelGGL(k_copy_slices<true>, dim3((unsigned)grid), dim3(p.threads), 0, s, a);
+        hipLaunchKernelGGL(k_copy_entries, dim3((unsigned)grid), dim3(p.threads), 0, s, a);
     return hipGetLastError();
 }
 
