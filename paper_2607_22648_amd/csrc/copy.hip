@@ -1142,7 +1142,7 @@ hipError_t copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache, int64_
     a.total = GATHER ? sc.nslices : sc.total;  // a gather has at most one slice per entry
     a.entries = (int64_t)R * max_blocks;
     const int64_t bound = a.entries * a.groups;  // units if every entry moves
-    const int32_t threads = p.threads;
+    const int32_t threads = GATHER ? p.gather_threads : p.threads;
     int64_t grid = copy_grid(p, GATHER, threads, bound);
     if (grid < 1) return hipSuccess;
     if (p.tier.host_blocks > 0) {

@@ -102,10 +102,11 @@ struct CopyPlan {
     int32_t chunks_per_block;  // 2 * layers
     int32_t chunks_per_group;  // chunks one copy unit moves
     int32_t threads;           // workgroup size of the copy kernel
+    int32_t gather_threads;    // the same of a gather
     int32_t grid;              // workgroups of the copy kernel, 0 = chosen per call
     int32_t gather_grid;       // most workgroups of a gather (one per unit below that)
     int32_t loop_grid;         // workgroups of a looping (sparse) copy
-    int32_t host_grid;         // workgroups of the looping copy of host-tier rows
+    int32_t host_grid;         // workgroups that loop over host-tier rows
     DevState* state;
     TierView tier;
     // per-layer slab sizes (null when every layer has chunk_bytes): the
