@@ -384,6 +384,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(SelectArgs a) {
     const int32_t last = E > 0 ? E - 1 : 0;
 #pragma unroll
     for (int k = 0; k < kSmallPer; ++k) {
+        id[k] = cb[k] = -1;
+        mr[k] = made[k] = 0;
+        if (k * kSmallThreads >= E) continue;  // uniform, here and below
         const int32_t s = E > 0 ? min(k * kSmallThreads + t, last) : 0;
         id[k] = E > 0 ? a.ids[s] : -1;
         cb[k] = E > 0 ? a.block_table[s] : -1;
@@ -395,6 +398,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(SelectArgs a) {
     int32_t bad = 0;
 #pragma unroll
     for (int k = 0; k < kSmallPer; ++k) {
+        p[k].row = 0;
+        p[k].cb = -1;
+        dm[k] = hm[k] = 0;
+        if (k * kSmallThreads >= E) {
+            if (lane == 0) wc[k * kSmallWaves + wv] = wch[k * kSmallWaves + wv] = 0;
+            continue;
+        }
         const int32_t s = k * kSmallThreads + t;
         const int32_t r = s / (a.max_blocks > 0 ? a.max_blocks : 1), b = s - r * a.max_blocks;
         const int32_t n = GATHER ? (mr[k] < 0 ? 0 : (mr[k] < a.max_blocks ? mr[k] : a.max_blocks))
