@@ -56,6 +56,8 @@ struct ptstore {
     DevState* state;
     void* insert_scratch;
     size_t insert_scratch_size;
+    uint64_t insert_table_cap;  // batch-table entries at its start, kept empty between calls
+    bool insert_dirty;          // an insert failed between filling and emptying the table
     // descriptor-list scratch per stream, so that lookups and gathers on
     // different streams may run at the same time
     struct StreamScratch {
@@ -901,16 +903,31 @@ int ptstore_insert(ptstore_t* s, const int32_t* tokens, const int64_t* offsets, 
     DeviceScope dev(s);
     if (dev.rc) return dev.rc;
     hipStream_t st = (hipStream_t)stream;
-    uint64_t tn;
-    const size_t need = insert_scratch_bytes(R, max_blocks, &tn);
-    hipError_t e;
-    if (need > s->insert_scratch_size && capturing(st))
+    const uint64_t entries = insert_table_entries(R, max_blocks);
+    hipError_t e = hipSuccess;
+    const bool fits = entries <= s->insert_table_cap &&
+                      insert_scratch_bytes(R, max_blocks, s->insert_table_cap) <= s->insert_scratch_size;
+    if ((!fits || s->insert_dirty) && capturing(st))
         return fail(PTSTORE_ERR_INVALID, "a captured insert needs a larger scratch than the store "
                     "has: run an insert of that size before capturing");
-    int rc2 = ensure_scratch(&s->insert_scratch, &s->insert_scratch_size, need, st, "ptstore_insert: scratch");
-    if (rc2) return rc2;
+    if (!fits) {
+        const uint64_t table = entries > s->insert_table_cap ? entries : s->insert_table_cap;
+        s->insert_table_cap = 0;  // until the new scratch has its empty table
+        size_t need = insert_scratch_bytes(R, max_blocks, table);
+        if (need <= s->insert_scratch_size) need = s->insert_scratch_size + 1;  // never moved in place
+        const int rc2 = ensure_scratch(&s->insert_scratch, &s->insert_scratch_size, need, st,
+                                       "ptstore_insert: scratch");
+        if (rc2) return rc2;
+        s->insert_table_cap = table;
+        s->insert_dirty = true;
+    }
+    if (s->insert_dirty) {  // a new table, or one a failed call left half-filled
+        e = launch_empty_batch(s->insert_scratch, s->insert_table_cap, st);
+        if (e != hipSuccess) return fail(PTSTORE_ERR_HIP, "ptstore_insert: empty table", e);
+        s->insert_dirty = false;
+    }
     InsertScratch sc;
-    insert_scratch_carve(s->insert_scratch, R, max_blocks, &sc);
+    insert_scratch_carve(s->insert_scratch, R, max_blocks, s->insert_table_cap, &sc);
     InsertTarget tgt{s->slots, s->parent, s->tokens, s->capacity};
     Batch b{tokens, offsets, n_tokens, R, max_blocks};
     {
@@ -922,6 +939,7 @@ int ptstore_insert(ptstore_t* s, const int32_t* tokens, const int64_t* offsets, 
             e = launch_evict(ix, tgt, s->evs, st);
         }
         if (e == hipSuccess) e = launch_insert_commit(ix, tgt, s->evs, b, sc, m_out, ids, created, st);
+        if (e != hipSuccess) s->insert_dirty = true;
     }
     return e == hipSuccess ? PTSTORE_OK : fail(PTSTORE_ERR_HIP, "ptstore_insert: launch", e);
 }

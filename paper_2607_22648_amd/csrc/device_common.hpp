@@ -173,6 +173,14 @@ __device__ inline uint64_t slot_of(uint64_t ikey, uint64_t seed, uint64_t mask) 
     return mix64(ikey ^ seed) & mask;
 }
 
+// Name of a new block in an insert's batch table: its index key and its depth
+// (only the depth's parity with the weak test tags). The top bit is clear,
+// so a tag never equals the empty marker.
+__device__ inline unsigned long long batch_tag(uint64_t ikey, int32_t b, uint64_t slot_seed, uint32_t weak_tag) {
+    const uint64_t d = weak_tag ? (uint64_t)(b & 1) : (uint64_t)b;
+    return mix64(ikey ^ (0x9E3779B97F4A7C15ull * (d + 1)) ^ ~slot_seed) & 0x7FFFFFFFFFFFFFFFull;
+}
+
 // 64-bit wavefront shuffles built from 32-bit ones.
 __device__ inline uint64_t shfl_u64(uint64_t v, int src) {
     uint32_t lo = __shfl((int)(uint32_t)v, src, kWave);

@@ -10,12 +10,11 @@
 //
 //   match      match every request against the store as it was (m0, ids) and
 //              write the chained keys of all its blocks (the key of block b is
-//              a function of the whole prefix up to b); empties the batch
-//              table on the side (lookup.hip, kInsert)
-//   claim      lane per missing block b >= m0: the block claims or joins the
-//              batch-table entry named by (key, depth) and records in it the
-//              smallest request that needs it; the block that claims an entry
-//              also records its depth there
+//              a function of the whole prefix up to b). Each missing block
+//              b >= m0 claims or joins the batch-table entry named by (key,
+//              depth) and records in it the smallest request that needs it;
+//              the block that claims an entry also records its depth there
+//              (lookup.hip, kInsert)
 //   verify     lane per block: the entry must hold the block's depth (else
 //              blocks of two depths, possibly of one request, share it), and
 //              the entry's smallest request o must hold the same prefix. It
@@ -23,15 +22,17 @@
 //              requests' first missing block under the same stored parent, or
 //              both requests' blocks b-1 sit in the same entry (by induction,
 //              equal prefixes). Any failure -- a collision of names between
-//              different prefixes -- raises a flag. The same pass counts, per
-//              request, the blocks it is the first (smallest r) to need
+//              different prefixes -- raises a flag. The same pass notes every
+//              block's owner, the first (smallest r) request to need it, and
+//              counts each request's own
 //   rank       one workgroup. Only when the flag is up it first redoes the
 //              claim exactly: the table is cleared and rebuilt one block after
 //              another per request, each block named by (entry of its parent,
 //              its tokens); slower, same result. Then the exclusive scan of
 //              the counts gives every request its first rank; the store count
 //              advances, clipped at capacity
-//   publish    lane per block: id, created, m_out, block metadata, index slot
+//   publish    lane per block: id, created, m_out, block metadata, index slot;
+//              empties the batch-table entries the batch used
 //
 // Ranks need no per-block pass: whoever needs a block also needs its parent,
 // so the blocks a request is the first to need are its last cnt[r] ones, and
@@ -45,11 +46,13 @@
 //
 // What bounds a call is the number of dependent launches, about 4.6 us each
 // for batches of up to a few hundred requests, not the work in them. Hence
-// five kernels (without eviction, or with a small store's, all of whose
+// four kernels (without eviction, or with a small store's, all of whose
 // eviction runs inside rank), where lookup, key hashing, two table clears,
 // claim, exact claim, verify, count, scan, assign, publish and touch had
 // been launches of their own; each wave has one 64-block window of one
-// request, so that a request of many windows is not walked by one wave.
+// request, so that a request of many windows is not walked by one wave. The
+// claim can run inside the match because the batch table is empty whenever
+// an insert begins: publish leaves it so.
 //
 // With eviction on, verify also marks the blocks the batch matched
 // (protected), rank computes how many blocks must be evicted and frees them
@@ -60,12 +63,6 @@
 #include "evict_small.hpp"
 
 namespace ptsd {
-
-struct alignas(16) BatchEntry {
-    unsigned long long word;  // claim: tag of (key, depth); exact: (parent label << 32) | token position
-    int32_t owner;            // smallest request that needs this block
-    int32_t depth;            // depth of the claiming block (exact claim: -1)
-};
 
 namespace {
 
@@ -113,15 +110,6 @@ __device__ inline void copy_tokens(int32_t* __restrict__ dst, const int32_t* __r
     for (int i = 0; i < bt; ++i) dst[i] = src[i];
 }
 
-// Name of a new block in the batch table: its chained key and its depth
-// (only the depth's parity with the weak test tags). The top bit is clear,
-// so a tag never equals the empty marker.
-__device__ inline unsigned long long tag_of(uint64_t key, int32_t b, const HashTables& ht) {
-    const uint64_t d = ht.weak_tag ? (uint64_t)(b & 1) : (uint64_t)b;
-    return mix64(index_key(key, ht) ^ (0x9E3779B97F4A7C15ull * (d + 1)) ^ ~ht.slot_seed) &
-           0x7FFFFFFFFFFFFFFFull;
-}
-
 struct InsertArgs {
     IndexView ix;
     InsertTarget tgt;
@@ -163,35 +151,6 @@ __device__ inline WaveOf wave_of(const Batch& bat) {
     return v;
 }
 
-__global__ __launch_bounds__(kThreads) void k_claim(InsertArgs a) {
-    const WaveOf v = wave_of(a.bat);
-    if (!v.any) return;
-    const int64_t i = v.r * a.bat.max_blocks + v.b;
-    const int32_t b = v.b;
-    const bool mine = b >= a.sc.m0[v.r] && b < a.sc.nblk[v.r];
-    if (!ballot64(mine)) return;
-    BatchEntry* __restrict__ tab = reinterpret_cast<BatchEntry*>(a.sc.table);
-    unsigned long long cas = 0, fails = 0;
-    if (mine) {
-        const unsigned long long tag = tag_of(a.sc.keys[i], b, *a.ix.ht);
-        uint64_t pos = tag & a.sc.table_mask;
-        while (true) {
-            const unsigned long long prev = atomicCAS(&tab[pos].word, kEmptyKey, tag);
-            ++cas;
-            if (prev == kEmptyKey) {
-                tab[pos].depth = b;  // read by verify, a kernel later
-                break;
-            }
-            if (prev == tag) break;
-            ++fails;
-            pos = (pos + 1) & a.sc.table_mask;
-        }
-        atomicMin(&tab[pos].owner, (int32_t)v.r);
-        a.sc.label[i] = (int32_t)pos;
-    }
-    count_cas(a, cas, fails, v.lane);
-}
-
 __global__ __launch_bounds__(kThreads) void k_verify(InsertArgs a) {
     const WaveOf v = wave_of(a.bat);
     if (!v.any) return;
@@ -201,13 +160,14 @@ __global__ __launch_bounds__(kThreads) void k_verify(InsertArgs a) {
     if (a.ev.on && b < m0)  // a block this request matched: not evicted by this insert
         a.ev.prot[a.ids[r * maxb + b]] = (int32_t)a.ix.state->ev_epoch;
     if (v.w * kWave + kWave <= m0 || v.w * kWave >= n) return;  // no new block in the window
-    const BatchEntry* __restrict__ tab = reinterpret_cast<const BatchEntry*>(a.sc.table);
+    const BatchEntry* __restrict__ tab = a.sc.table;
     bool ok = true, own = false;
     if (b >= m0 && b < n) {
         const int32_t label = a.sc.label[r * maxb + b];
         const BatchEntry te = tab[label];
         const int64_t o = te.owner;
         own = o == r;
+        a.sc.owner[r * maxb + b] = te.owner;  // for publish, which empties the table
         ok = te.depth == b;  // else the entry was claimed at another depth
         if (ok && !own) {
             const int32_t om0 = a.sc.m0[o];
@@ -227,6 +187,14 @@ __global__ __launch_bounds__(kThreads) void k_verify(InsertArgs a) {
     if (v.lane == 0 && c) atomicAdd(&a.sc.cnt[r], c);
 }
 
+__device__ inline BatchEntry empty_entry() {
+    BatchEntry e;
+    e.word = kEmptyKey;
+    e.owner = kNoOwner;
+    e.depth = -1;
+    return e;
+}
+
 // The exact claim, by one workgroup: one block after another per request
 // (runs only on a collision). Labels, owners and counts are made anew. The
 // entries and counts are changed by device-scope atomics, so what an earlier
@@ -235,16 +203,10 @@ __device__ inline void claim_exact(const InsertArgs& a) {
     const int t = threadIdx.x, nt = blockDim.x;
     const int bt = a.ix.block_tokens;
     const int64_t maxb = a.bat.max_blocks;
-    BatchEntry* __restrict__ tab = reinterpret_cast<BatchEntry*>(a.sc.table);
+    BatchEntry* __restrict__ tab = a.sc.table;
     const HashTables* __restrict__ ht = a.ix.ht;
     if (t == 0) atomicAdd(&a.ix.state->insert_fallbacks, 1ull);
-    for (uint64_t i = t; i <= a.sc.table_mask; i += nt) {
-        BatchEntry e;
-        e.word = kEmptyKey;
-        e.owner = 0x7FFFFFFF;
-        e.depth = -1;
-        tab[i] = e;
-    }
+    for (uint64_t i = t; i <= a.sc.table_mask; i += nt) tab[i] = empty_entry();
     for (int64_t r = t; r < a.bat.R; r += nt) a.sc.cnt[r] = 0;
     __threadfence();
     __syncthreads();
@@ -274,9 +236,12 @@ __device__ inline void claim_exact(const InsertArgs& a) {
     __syncthreads();
     for (int64_t r = t; r < a.bat.R; r += nt) {
         int32_t c = 0;
-        for (int32_t b = a.sc.m0[r]; b < a.sc.nblk[r]; ++b)
-            c += __hip_atomic_load(&tab[a.sc.label[r * maxb + b]].owner, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT) == (int32_t)r;
+        for (int32_t b = a.sc.m0[r]; b < a.sc.nblk[r]; ++b) {
+            const int32_t o = __hip_atomic_load(&tab[a.sc.label[r * maxb + b]].owner, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+            a.sc.owner[r * maxb + b] = o;
+            c += o == (int32_t)r;
+        }
         a.sc.cnt[r] = c;
     }
     __threadfence();
@@ -399,13 +364,11 @@ __device__ inline void reenter_survivors(const InsertArgs& a) {
     }
 }
 
-// The id of a request's new block b, whose entry in the batch table is
-// `label`: -1 if it is refused.
-__device__ inline int32_t new_id(const InsertArgs& a, int32_t label, int32_t b, long long old,
-                                 long long fresh, long long nv, int32_t* owner) {
-    const BatchEntry* __restrict__ tab = reinterpret_cast<const BatchEntry*>(a.sc.table);
-    *owner = tab[label].owner;
-    const long long k = (long long)a.sc.start[*owner] + b;  // rank among the batch's new blocks
+// The id of a new block at depth b that `owner` is the first to need: -1 if
+// it is refused.
+__device__ inline int32_t new_id(const InsertArgs& a, int32_t owner, int32_t b, long long old,
+                                 long long fresh, long long nv) {
+    const long long k = (long long)a.sc.start[owner] + b;  // rank among the batch's new blocks
     if (k < fresh) return (int32_t)(old + k);
     return k - fresh < nv ? a.ev.victims[k - fresh] : -1;
 }
@@ -429,15 +392,17 @@ __global__ __launch_bounds__(kThreads) void k_publish(InsertArgs a) {
     unsigned long long cas = 0, fails = 0, tombs_taken = 0;
     const bool is_new = b >= m0 && b < n;
     int32_t id = -1, owner = -1;
-    if (is_new) id = new_id(a, a.sc.label[r * maxb + b], b, old, fresh, nv, &owner);
-    else if (a.ev.on && b < m0) id = row[b];
+    if (is_new) {
+        owner = a.sc.owner[r * maxb + b];
+        a.sc.table[a.sc.label[r * maxb + b]] = empty_entry();  // nothing reads it any more
+        id = new_id(a, owner, b, old, fresh, nv);
+    } else if (a.ev.on && b < m0) id = row[b];
     int32_t parent = __shfl_up(id, 1, kWave);
     if (is_new) {
-        int32_t po;
         if (b == m0)
             parent = m0 == 0 ? -1 : row[m0 - 1];
         else if (v.lane == 0)
-            parent = new_id(a, a.sc.label[r * maxb + b - 1], b - 1, old, fresh, nv, &po);
+            parent = new_id(a, a.sc.owner[r * maxb + b - 1], b - 1, old, fresh, nv);
         // refusals are a suffix of the request: one lane holds the cut
         if (id < 0 && (b == m0 || parent >= 0)) a.m_out[r] = b;
         if (id >= 0 && b == n - 1) a.m_out[r] = n;
@@ -491,38 +456,56 @@ __global__ __launch_bounds__(kThreads) void k_publish(InsertArgs a) {
 
 }  // namespace
 
-size_t insert_scratch_bytes(int32_t R, int32_t max_blocks, uint64_t* table_entries) {
+namespace {
+size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+__global__ void k_empty_batch(BatchEntry* t, uint64_t n) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        t[i] = empty_entry();
+}
+}  // namespace
+
+uint64_t insert_table_entries(int32_t R, int32_t max_blocks) {
     const uint64_t rb = (uint64_t)R * (uint64_t)max_blocks;
     uint64_t t = 64;
     while (t < 2 * rb) t <<= 1;
-    *table_entries = t;
-    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    return up(rb * 8) + up((size_t)R * 4) + up(rb * 4) + up((size_t)R * 4) * 3 +
-           up(t * sizeof(BatchEntry)) + 256;
+    return t;
 }
 
-void insert_scratch_carve(void* base, int32_t R, int32_t max_blocks, InsertScratch* out) {
-    uint64_t t;
-    insert_scratch_bytes(R, max_blocks, &t);
-    const uint64_t rb = (uint64_t)R * (uint64_t)max_blocks;
-    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+size_t insert_scratch_bytes(int32_t R, int32_t max_blocks, uint64_t table_cap) {
+    const size_t rb = (size_t)R * (size_t)max_blocks;
+    return up256(table_cap * sizeof(BatchEntry)) + up256(rb * 8) + 2 * up256(rb * 4) +
+           4 * up256((size_t)R * 4) + 256;
+}
+
+void insert_scratch_carve(void* base, int32_t R, int32_t max_blocks, uint64_t table_cap,
+                          InsertScratch* out) {
+    const size_t rb = (size_t)R * (size_t)max_blocks;
     uint8_t* p = static_cast<uint8_t*>(base);
-    out->keys = reinterpret_cast<uint64_t*>(p);
-    p += up(rb * 8);
-    out->m0 = reinterpret_cast<int32_t*>(p);
-    p += up((size_t)R * 4);
-    out->label = reinterpret_cast<int32_t*>(p);
-    p += up(rb * 4);
-    out->nblk = reinterpret_cast<int32_t*>(p);
-    p += up((size_t)R * 4);
-    out->cnt = reinterpret_cast<int32_t*>(p);
-    p += up((size_t)R * 4);
-    out->start = reinterpret_cast<int32_t*>(p);
-    p += up((size_t)R * 4);
-    out->table = p;
-    out->table_mask = t - 1;
-    p += up(t * sizeof(BatchEntry));
+    auto take = [&](size_t bytes) {
+        uint8_t* q = p;
+        p += up256(bytes);
+        return q;
+    };
+    out->table = reinterpret_cast<BatchEntry*>(take(table_cap * sizeof(BatchEntry)));
+    out->table_mask = insert_table_entries(R, max_blocks) - 1;
+    out->keys = reinterpret_cast<uint64_t*>(take(rb * 8));
+    out->label = reinterpret_cast<int32_t*>(take(rb * 4));
+    out->owner = reinterpret_cast<int32_t*>(take(rb * 4));
+    out->m0 = reinterpret_cast<int32_t*>(take((size_t)R * 4));
+    out->nblk = reinterpret_cast<int32_t*>(take((size_t)R * 4));
+    out->cnt = reinterpret_cast<int32_t*>(take((size_t)R * 4));
+    out->start = reinterpret_cast<int32_t*>(take((size_t)R * 4));
     out->collision = reinterpret_cast<unsigned int*>(p);
+}
+
+hipError_t launch_empty_batch(void* table, uint64_t entries, hipStream_t s) {
+    uint64_t g = (entries + 255) / 256;
+    if (g > 65536) g = 65536;
+    hipLaunchKernelGGL(k_empty_batch, dim3((unsigned)g), dim3(256), 0, s, static_cast<BatchEntry*>(table),
+                       entries);
+    return hipGetLastError();
 }
 
 namespace {
@@ -539,12 +522,10 @@ hipError_t launch_insert_match(const IndexView& ix, const InsertTarget& tgt, con
     IndexView quiet = ix;  // the insert's own match is not an access
     quiet.freq = nullptr;
     quiet.prio = nullptr;
-    const InsertMatch im{sc.keys, sc.nblk, sc.cnt, sc.table, sc.table_mask + 1, sc.collision, ev.on};
+    const InsertMatch im{sc.keys, sc.label, sc.nblk, sc.cnt, sc.table, sc.table_mask, sc.collision, ev.on};
     if ((e = launch_match(quiet, b, sc.m0, ids, im, s)) != hipSuccess) return e;
     InsertArgs a{quiet, tgt, ev, b, sc, m_out, ids, created};
     const unsigned wgrid = window_grid(b);
-    hipLaunchKernelGGL(k_claim, dim3(wgrid), dim3(kThreads), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_verify, dim3(wgrid), dim3(kThreads), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev.on && evicts_in_rank(tgt.capacity))

@@ -77,6 +77,15 @@ struct Batch {
     int32_t max_blocks;
 };
 
+// An entry of an insert's batch table, which names the batch's new blocks.
+// Empty entries hold kEmptyKey, kNoOwner and any depth.
+struct alignas(16) BatchEntry {
+    unsigned long long word;  // claim: tag of (key, depth); exact: (parent label << 32) | token position
+    int32_t owner;            // smallest request that needs this block
+    int32_t depth;            // depth of the claiming block (exact claim: -1)
+};
+constexpr int32_t kNoOwner = 0x7FFFFFFF;
+
 // lookup.hip
 hipError_t launch_lookup(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids,
                          hipStream_t s);
@@ -84,10 +93,11 @@ hipError_t launch_lookup(const IndexView& ix, const Batch& b, int32_t* m, int32_
 // kernels need of it.
 struct InsertMatch {
     uint64_t* keys;           // [R][max_blocks] out: chained key of every whole block
+    int32_t* label;           // [R][max_blocks] out: batch-table entry of each new block
     int32_t* nblk;            // [R] out: blocks of each request (0 for a malformed one)
     int32_t* cnt;             // [R] out: zeroed
-    void* table;              // table_n 16-byte batch entries, emptied
-    uint64_t table_n;
+    BatchEntry* table;        // the batch table, empty; the new blocks claim their entries
+    uint64_t table_mask;
     unsigned int* collision;  // lowered
     int32_t ev_on;            // 1: advance the eviction epoch
 };
@@ -195,20 +205,28 @@ hipError_t launch_copy_rows(const CopyPlan& p, const Pair* pairs, const unsigned
                             int64_t max_pairs, hipStream_t s);
 
 // insert.hip
-struct BatchEntry;  // defined in insert.hip
+// The batch table sits at the start of the scratch, table_cap entries that
+// every insert leaves empty; a call uses its first table_mask + 1.
 struct InsertScratch {
+    BatchEntry* table;
+    uint64_t table_mask;
     uint64_t* keys;       // [R][max_blocks]
     int32_t* m0;          // [R] match length before the insert
     int32_t* nblk;        // [R] blocks of each request
     int32_t* label;       // [R][max_blocks] batch-table slot of each new block
     int32_t* cnt;         // [R] blocks each request is the first to need (its last ones)
     int32_t* start;       // [R] rank of its block b among the batch's new blocks is start + b
-    void* table;          // batch table, table_mask + 1 entries of 16 bytes
-    uint64_t table_mask;
+    int32_t* owner;       // [R][max_blocks] smallest request that needs each new block
     unsigned int* collision;  // set when the fast claim must be redone exactly
 };
-size_t insert_scratch_bytes(int32_t R, int32_t max_blocks, uint64_t* table_entries);
-void insert_scratch_carve(void* base, int32_t R, int32_t max_blocks, InsertScratch* out);
+// Batch-table entries a call needs, and the scratch bytes of a call after a
+// table of table_cap entries; the carve lays a call out in such a scratch.
+uint64_t insert_table_entries(int32_t R, int32_t max_blocks);
+size_t insert_scratch_bytes(int32_t R, int32_t max_blocks, uint64_t table_cap);
+void insert_scratch_carve(void* base, int32_t R, int32_t max_blocks, uint64_t table_cap,
+                          InsertScratch* out);
+// Empty batch table in a new scratch.
+hipError_t launch_empty_batch(void* table, uint64_t entries, hipStream_t s);
 
 struct InsertTarget {
     Slot* slots;

@@ -24,8 +24,8 @@
 // the final F whatever order the atomics land in.
 //
 // An insert's match is the same walk (kInsert): it also writes every block's
-// chained key, going on to hash the windows past the first miss, and readies
-// the insert's work space (see insert.hip).
+// chained key, going on to hash the windows past the first miss, and claims
+// the batch-table entries of the blocks past the match (see insert.hip).
 #include "kernels.hpp"
 
 namespace ptsd {
@@ -367,13 +367,11 @@ __device__ inline int32_t request_blocks(const Batch& b, int64_t r, int bt, int 
 enum Mode {
     kPlain,   // nothing
     kTouch,   // count accesses (eviction on)
-    kInsert,  // an insert's match: keys of every block, work space made ready
+    kInsert,  // an insert's match: keys of every block, claims of the new ones
 };
 
-// An insert's work space before its claim: the batch table empty (every
-// workgroup clears its share; the stores are not waited for), the collision
-// flag down, and the eviction epoch advanced, so that a replayed capture
-// marks its own matches.
+// The collision flag down, and the eviction epoch advanced, so that a
+// replayed capture marks its own matches.
 __device__ inline void insert_setup(const InsertMatch& im, DevState* st) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *im.collision = 0;
@@ -382,10 +380,28 @@ __device__ inline void insert_setup(const InsertMatch& im, DevState* st) {
             st->ev_epoch = e >= 0x7FFFFFFFull ? 1ull : e;
         }
     }
-    uint4* t = static_cast<uint4*>(im.table);  // {word, owner, depth}
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < im.table_n;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        t[i] = make_uint4((uint32_t)kEmptyKey, (uint32_t)(kEmptyKey >> 32), 0x7FFFFFFFu, 0xFFFFFFFFu);
+}
+
+// Request r's new block b, index key ik, claims or joins the batch-table
+// entry of its name. The table holds at least twice as many entries as the
+// batch has blocks.
+__device__ inline void claim(const InsertMatch& im, int64_t at, int64_t r, int32_t b, uint64_t ik,
+                             uint64_t slot_seed, uint32_t weak_tag, unsigned* cas, unsigned* fails) {
+    const unsigned long long tag = batch_tag(ik, b, slot_seed, weak_tag);
+    uint64_t pos = tag & im.table_mask;
+    while (true) {
+        const unsigned long long prev = atomicCAS(&im.table[pos].word, kEmptyKey, tag);
+        ++*cas;
+        if (prev == kEmptyKey) {
+            im.table[pos].depth = b;  // read by verify, a kernel later
+            break;
+        }
+        if (prev == tag) break;
+        ++*fails;
+        pos = (pos + 1) & im.table_mask;
+    }
+    atomicMin(&im.table[pos].owner, (int32_t)r);
+    im.label[at] = (int32_t)pos;
 }
 
 template <int BT, Mode MODE>
@@ -410,7 +426,8 @@ __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, in
     uint64_t carry_key = cc.root_key;
     int32_t carry_id = -1;  // the root
     int32_t m = 0;
-    unsigned probes = 0, cmps = 0;
+    unsigned probes = 0, cmps = 0, cas = 0, fails = 0;
+    const uint32_t weak_tag = MODE == kInsert ? ix.ht->weak_tag : 0;
     int w0 = 0;
     bool done = false;
     for (; w0 < n && !done; w0 += kWave) {
@@ -444,6 +461,8 @@ __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, in
                 cand = probe(ix, ik, (pos + 1) & ix.slot_mask, win, true, prev, &pos, &cpar,
                              &probes, &cmps);
         }
+        if (MODE == kInsert && active && lane >= first_bad)
+            claim(im, r * bat.max_blocks + b, r, b, ik, cc.slot_seed, weak_tag, &cas, &fails);
         if (active) row[b] = lane < first_bad ? cand : -1;
         if (TOUCH && active && lane < first_bad) {
             const uint64_t f = atomicAdd((unsigned long long*)&ix.freq[cand], 1ull) + 1ull;
@@ -471,6 +490,10 @@ __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, in
         CounterSlot* cs = counter_slot(ix.state);
         wave_count(&cs->probes, probes, lane);
         wave_count(&cs->token_compares, cmps, lane);
+        if (MODE == kInsert) {
+            wave_count(&cs->cas_attempts, cas, lane);
+            wave_count(&cs->cas_failures, fails, lane);
+        }
     }
 }
 
@@ -513,7 +536,8 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
     uint64_t carry_key = cc.root_key;
     int32_t carry_id = -1;  // the root
     int32_t m = n;
-    unsigned probes = 0, cmps = 0;
+    unsigned probes = 0, cmps = 0, cas = 0, fails = 0;
+    const uint32_t weak_tag = MODE == kInsert ? ix.ht->weak_tag : 0;
     int r0 = 0;  // first block of the round
     for (; r0 < n; r0 += W * kWave) {
         const int b = r0 + wv * kWave + lane;
@@ -567,6 +591,8 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
                              &probes, &cmps);
         }
         const int rel = wv * kWave + lane;
+        if (MODE == kInsert && active && rel >= fail)
+            claim(im, r * bat.max_blocks + b, r, b, ik, cc.slot_seed, weak_tag, &cas, &fails);
         if (active) row[b] = rel < fail ? cand : -1;
         if (TOUCH && active && rel < fail) {
             const uint64_t fq = atomicAdd((unsigned long long*)&ix.freq[cand], 1ull) + 1ull;
@@ -603,7 +629,10 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
             uint64_t carry = carry_key;
             for (int i = 0; i < wv; ++i) carry = addmod61(mulmod61(p64, carry), sh_off[i]);
             const uint64_t k = addmod61(mulmod61(cc.lane_pow, carry), sl);
-            if (b < n) im.keys[r * bat.max_blocks + b] = k;
+            if (b < n) {
+                im.keys[r * bat.max_blocks + b] = k;
+                claim(im, r * bat.max_blocks + b, r, b, index_key(k, cc), cc.slot_seed, weak_tag, &cas, &fails);
+            }
             if (wv == W - 1 && lane == kWave - 1) sh_klast = k;
             __syncthreads();
             carry_key = sh_klast;
@@ -613,6 +642,10 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
         CounterSlot* cs = counter_slot(ix.state);
         wave_count(&cs->probes, probes, lane);
         wave_count(&cs->token_compares, cmps, lane);
+        if (MODE == kInsert) {
+            wave_count(&cs->cas_attempts, cas, lane);
+            wave_count(&cs->cas_failures, fails, lane);
+        }
     }
 }
 
