@@ -156,7 +156,9 @@ def _requests(offsets: torch.Tensor) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the handle alone: building a torch.cuda.Stream to read it from takes
+        # longer than the rest of a short call's checks
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
