@@ -219,8 +219,8 @@ CopyPlan copy_plan(ptstore_t* s) {
     // units of 1,048,576 possible), 512 rounds copy in 7.46 ms against 8.11
     // at 2,048 rounds and 7.42 with exactly one workgroup per unit; on the 8B
     // shape (759,808 units) 12.38 against 12.47 and 12.21. A scatter, whose units are
-    // sparse, launches 16 rounds that loop (4 rounds: 7 % slower on a large
-    // scatter; 128 rounds: 45 % slower on a small one).
+    // sparse, launches at most 16 rounds that loop (4 rounds: 7 % slower on a
+    // large scatter; 128 rounds: 45 % slower on a small one).
     const int resident = s->cus * (2048 / s->threads);
     // A gather of uniform slabs, one chunk per unit, runs in workgroups of 512
     // threads: an empty one costs about half as much to launch, and four of

@@ -39,8 +39,8 @@
 // Only blocks that are really copied cost work, however sparse they are in
 // the [request][block] arrays (a few created blocks per insert, half the
 // requests missing the store). The default copy shape gives each
-// 1024-thread workgroup one chunk per unit (two vectors per thread for a
-// 32 KiB chunk). The copies are pure HBM streaming: no MFMA. LDS holds the
+// workgroup one chunk per unit: four vectors per thread of a 32 KiB chunk in a
+// gather of several requests (512 threads), two in any other call (1024). The copies are pure HBM streaming: no MFMA. LDS holds the
 // row tables of the grouping step and the per-layer kernel's table of layer
 // bases.
 #include "kernels.hpp"
@@ -815,11 +815,11 @@ __device__ inline unsigned long long unit_desc(unsigned long long unit, int grou
 
 // The (descriptor, chunk group) units are visited grid-stride. The host
 // picks the grid: a gather launches one workgroup per possible unit, up to
-// 512 times what the device holds at once, so the dense front of the list
+// 262,144 on 256 compute units, so the dense front of the list
 // runs in hardware dispatch order (neighbouring workgroups copy neighbouring
 // chunks; past the cap a workgroup also takes the unit one grid further on,
 // and workgroups past the end exit at once); a scatter, whose created blocks
-// are sparse, launches 16 times what the device holds, looping.
+// are sparse, launches a looping grid (loop_grid).
 // Scatter, uniform slabs: a unit is (pair, group of chunks_per_group slabs).
 __global__ __launch_bounds__(1024) void k_copy_pairs(CopyArgs a) {
     const Share h = share_of(a);
