@@ -404,7 +404,7 @@ __device__ inline void claim(const InsertMatch& im, int64_t at, int64_t r, int32
     im.label[at] = (int32_t)pos;
 }
 
-template <int BT, Mode MODE>
+template <int BT, int MODE>
 __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, int32_t* __restrict__ m_out,
                                                      int32_t* __restrict__ ids_out, InsertMatch im) {
     constexpr bool TOUCH = MODE == kTouch;
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kThreads) void k_lookup(IndexView ix, Batch bat, in
 // first failing position decides; only when it found the right tokens under
 // another parent (a key collision) does that lane probe on, and the round is
 // checked again.
-template <int BT, Mode MODE, int W>
+template <int BT, int MODE, int W>
 __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch bat,
                                                            int32_t* __restrict__ m_out,
                                                            int32_t* __restrict__ ids_out, InsertMatch im) {
@@ -652,7 +652,7 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
 }  // namespace
 
 namespace {
-template <Mode MODE, int W>
+template <int MODE, int W>
 void launch_wide(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, const InsertMatch& im,
                  hipStream_t s) {
     const dim3 grid((unsigned)b.R), block(W * kWave);
@@ -664,7 +664,7 @@ void launch_wide(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, 
         hipLaunchKernelGGL((k_lookup_wide<0, MODE, W>), grid, block, 0, s, ix, b, m, ids, im);
 }
 
-template <Mode MODE>
+template <int MODE>
 hipError_t launch(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, const InsertMatch& im,
                   hipStream_t s) {
     // requests of more than one window: a workgroup per request, windows in
