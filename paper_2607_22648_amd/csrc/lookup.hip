@@ -580,7 +580,7 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
                 }
             const int fl = fw >= 0 ? sh_fail[fw] : kWave;
             const bool again = fw >= 0 && sh_retry[fw];
-            if (fw >= 0) fail = fw * kWave + fl;
+            fail = fw >= 0 ? fw * kWave + fl : W * kWave;  // anew in each check: a retry may clear it
             __syncthreads();  // every wave has read the round's flags
             if (!again) break;
             // keys of two different prefixes collided: that lane looks
