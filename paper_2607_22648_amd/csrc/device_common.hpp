@@ -55,12 +55,14 @@ struct alignas(128) CounterSlot {
 };
 
 // Eviction threshold search: digits of kSelBits bits over a key of at most
-// 128. The first kSelPasses digits are found over all candidates, the rest
-// over the few that agree with them.
+// 128. The first digits are found over all candidates, by up to kSelPasses
+// passes while more than kSelListMax candidates agree with the digits found
+// so far; the rest over a list of those that agree.
 constexpr int kSelBits = 11;
 constexpr int kSelBins = 1 << kSelBits;
-constexpr int kSelPasses = 2;
+constexpr int kSelPasses = 4;
 constexpr int kSelDone = kSelPasses + 1;
+constexpr unsigned kSelListMax = 1024;
 
 // Device-side counters and status of a store.
 struct DevState {
@@ -91,7 +93,9 @@ struct DevState {
     unsigned long long sel_need;        // rank of the threshold among what matches it
     unsigned int sel_range_done;        // workgroups finished the range pass
     unsigned int sel_done[kSelDone];    // workgroups finished per digit pass
-    unsigned int sel_list;              // candidates listed after those passes
+    unsigned int sel_known;             // digits found by the passes
+    unsigned int sel_bin;               // candidates that agree with them
+    unsigned int sel_list;              // candidates listed after the passes
     // what the search ranks: 0 = eviction candidates (ids below sel_hi_id
     // that the batch did not match, key (H, deeper, id)); 1 = the host tier,
     // ids sel_lo_id .. sel_hi_id-1, key (H descending, id)

@@ -22,22 +22,21 @@
 // takes the minimum and maximum of each field over the candidates; the key
 // then keeps only the bits in which candidates can differ,
 //   (H - Hmin) | (depth_max - depth) | (id - id_min),
-// left-aligned in 128 bits (typically some 40 bits wide). Two digit passes
-// over all candidates, each a 2048-bin histogram of the next 11 bits among
-// the keys that agree with the threshold found so far, whose last workgroup
-// to finish picks the digit; then the candidates that agree in those 22 bits
-// are listed, and the last workgroup finds the remaining digits over the
-// list alone. Then the victims are marked in a bit mask, their index slots
-// become tombstones, L takes their largest H, and a scan lists them by
+// left-aligned in 128 bits (typically some 40 bits wide). Digit passes over
+// all candidates, each a 2048-bin histogram of the next 11 bits among the
+// keys that agree with the threshold found so far, whose last workgroup to
+// finish picks the digit; once few candidates agree in the digits found,
+// they are listed, and the last workgroup finds the remaining digits over
+// the list alone. Then the victims are marked in a bit mask, their index
+// slots become tombstones, L takes their largest H, and a scan lists them by
 // ascending id, the order in which their ids are reused. When deleted slots
 // have piled up, the index is cleared instead and publish enters the
 // surviving blocks again.
 //
 // The work of a search is small (16 bytes per candidate and pass); what it
-// costs is launches, about 4.6 us each. Six here, where the twelve digit
-// passes, most of them empty, the scan, the list and two rebuild steps had
-// made seventeen. A store of up to 16,384 blocks runs none of this: see
-// evict_small.hpp.
+// costs is launches. Eight here, where the twelve digit passes, the scan,
+// the list and two rebuild steps had made seventeen. A store of up to 16,384
+// blocks runs none of this: see evict_small.hpp.
 #include "kernels.hpp"
 #include "evict_small.hpp"
 
@@ -160,9 +159,15 @@ __global__ __launch_bounds__(kThreads) void k_sel_range(EvictView ev, DevState* 
     st->sel_npass = (wp + wd + wi + kSelBits - 1) / kSelBits;
 }
 
-// One digit pass of the threshold search.
+// One digit pass of the threshold search. Past the first, it runs only while
+// more candidates agree with the threshold than one workgroup should list: a
+// block with far more accesses than the others widens H by up to twenty bits
+// or more, all of them equal among the candidates that matter, so that how
+// many digits it takes to tell those apart is not known beforehand.
 __global__ __launch_bounds__(kThreads) void k_sel_pass(EvictView ev, DevState* st, int pass) {
-    if (st->ev_want == 0 || st->ev_all || (unsigned)pass >= st->sel_npass) return;  // uniform
+    // uniform: the last workgroup changes these when all have read them
+    if (st->ev_want == 0 || st->ev_all || (unsigned)pass >= st->sel_npass) return;
+    if (pass > 1 && st->sel_bin <= kSelListMax) return;
     __shared__ unsigned int h[kSelBins];
     __shared__ unsigned int part[kThreads];
     __shared__ int last;
@@ -218,32 +223,35 @@ __global__ __launch_bounds__(kThreads) void k_sel_pass(EvictView ev, DevState* s
         const unsigned digit = (unsigned)(t * kPer + j);
         const u128 nt = thr | ((u128)digit << lo_bit);
         st->sel_need = need - cum;
+        st->sel_known = (unsigned)pass + 1;
+        st->sel_bin = h[digit];
         st->sel_hi = (uint64_t)(nt >> 64);
         st->sel_lo = (uint64_t)nt;
     }
 }
 
-// The digits past the first kSelPasses: the candidates that agree with the
+// The digits past those of the passes: the candidates that agree with the
 // threshold so far are listed (their ids, in the array the victims come into
-// later), and the last workgroup finds the rest over the list by itself.
-// The list is short -- in practice the blocks of one H and about one depth
-// -- and a list as long as the store only makes this one workgroup slower.
+// later), and the last workgroup finds the rest over the list by itself. The
+// list has at most kSelListMax entries unless all kSelPasses passes ran and
+// left more, in keys alike in their first 44 bits.
 constexpr int kFinishThreads = 1024;
 
 __global__ __launch_bounds__(kFinishThreads) void k_sel_finish(EvictView ev, DevState* st) {
-    if (st->ev_want == 0 || st->ev_all || st->sel_npass <= (unsigned)kSelPasses) return;  // uniform
+    if (st->ev_want == 0 || st->ev_all || st->sel_npass <= st->sel_known) return;  // uniform
     __shared__ uint32_t h[kSelBins];
     __shared__ uint32_t wsum[kFinishThreads / kWave], found[2];
     __shared__ int last;
     const int t = threadIdx.x, lane = t & (kWave - 1);
     const int64_t lo_id = (int64_t)st->sel_lo_id, hi_id = (int64_t)st->sel_hi_id;
     u128 thr = ((u128)st->sel_hi << 64) | (u128)st->sel_lo;
-    constexpr int kKnown = 128 - kSelBits * kSelPasses;  // key bits still open
+    const int known = (int)st->sel_known;
+    const int open = 128 - kSelBits * known;  // key bits not yet found
     for (int64_t base = lo_id + (int64_t)blockIdx.x * kFinishThreads; base < hi_id;
          base += (int64_t)gridDim.x * kFinishThreads) {
         const int64_t id = base + t;
         const bool in = id < hi_id && sel_candidate(ev, st, id) &&
-                        (sel_key(ev, st, id) >> kKnown) == (thr >> kKnown);
+                        (sel_key(ev, st, id) >> open) == (thr >> open);
         const unsigned long long mask = ballot64(in);
         unsigned at = 0;
         if (lane == 0 && mask) at = atomicAdd(&st->sel_list, (unsigned)__popcll(mask));
@@ -260,7 +268,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_sel_finish(EvictView ev, Dev
     uint32_t need = (uint32_t)st->sel_need;
     h[2 * t] = h[2 * t + 1] = 0;
     __syncthreads();
-    for (int pass = kSelPasses; pass < (int)st->sel_npass; ++pass) {
+    for (int pass = known; pass < (int)st->sel_npass; ++pass) {
         const int hi_bit = 128 - kSelBits * pass;
         const int lo_bit = hi_bit - kSelBits > 0 ? hi_bit - kSelBits : 0;
         const unsigned dmask = (1u << (hi_bit - lo_bit)) - 1u;
@@ -372,6 +380,8 @@ __global__ void k_rep_setup(DevState* st, TierView tier) {
     if (t < kSelDone) st->sel_done[t] = 0;
     if (t != 0) return;
     st->sel_list = 0;
+    st->sel_known = 0;
+    st->sel_bin = 0;
     const uint64_t count = st->count;
     st->sel_hot = 1;
     st->sel_lo_id = (uint64_t)tier.owned;

@@ -322,6 +322,8 @@ __global__ __launch_bounds__(kRankThreads) void k_rank(InsertArgs a) {
             st->ev_rebuild = 0;
             st->sel_range_done = 0;
             st->sel_list = 0;
+            st->sel_known = 0;
+            st->sel_bin = 0;
             for (int k = 0; k < kSelDone; ++k) st->sel_done[k] = 0;
             st->sel_npass = 0;
             st->sel_hot = 0;
