@@ -159,11 +159,14 @@ __global__ __launch_bounds__(kThreads) void k_sel_range(EvictView ev, DevState* 
     st->sel_npass = (wp + wd + wi + kSelBits - 1) / kSelBits;
 }
 
-// One digit pass of the threshold search. Past the first, it runs only while
+// One digit pass of the threshold search. Past the second, it runs only while
 // more candidates agree with the threshold than one workgroup should list: a
-// block with far more accesses than the others widens H by up to twenty bits
-// or more, all of them equal among the candidates that matter, so that how
-// many digits it takes to tell those apart is not known beforehand.
+// block with far more accesses than the others widens H by twenty bits or
+// more, all of them equal among the candidates that matter, so that how many
+// digits it takes to tell those apart is not known beforehand. Evicting 256
+// of 1,048,576 blocks, one of them with 2*10^7 accesses: 225 us in the
+// eviction's kernels; 272 with three passes, 4,500 with two, 245 with twelve
+// that all run. A pass that exits costs 1.7 us.
 __global__ __launch_bounds__(kThreads) void k_sel_pass(EvictView ev, DevState* st, int pass) {
     // uniform: the last workgroup changes these when all have read them
     if (st->ev_want == 0 || st->ev_all || (unsigned)pass >= st->sel_npass) return;
