@@ -44,6 +44,7 @@
 // row tables of the grouping step and the per-layer kernel's table of layer
 // bases.
 #include "kernels.hpp"
+#include "launch_rules.hpp"
 
 namespace ptsd {
 namespace {
@@ -776,6 +777,7 @@ struct CopyArgs {
     int32_t chunks_per_block;
     int32_t chunks_per_group;
     int32_t groups;            // ceil((c_hi - c_lo) / chunks_per_group)
+    int64_t range_bytes;       // bytes of chunks c_lo .. c_hi - 1 of a block
     int32_t c_lo, c_hi;        // chunks moved: 2*l0 .. 2*l1-1
     const int64_t* lbase;      // per-layer slab bases (null when uniform)
 };
@@ -819,7 +821,7 @@ __device__ inline unsigned long long unit_desc(unsigned long long unit, int grou
 // runs in hardware dispatch order (neighbouring workgroups copy neighbouring
 // chunks; past the cap a workgroup also takes the unit one grid further on,
 // and workgroups past the end exit at once); a scatter, whose created blocks
-// are sparse, launches a looping grid (loop_grid).
+// are sparse, launches a looping grid (scatter_grid).
 // Scatter, uniform slabs: a unit is (pair, group of chunks_per_group slabs).
 __global__ __launch_bounds__(1024) void k_copy_pairs(CopyArgs a) {
     const Share h = share_of(a);
@@ -1125,8 +1127,10 @@ CopyArgs copy_args(const CopyPlan& p, uint8_t* cache, int64_t cache_blocks, int3
     if (p.lbase) {  // units are kSpanBytes spans of the layer range
         const int64_t lo = p.lbase_host[l0], hi = p.lbase_host[l1];
         a.groups = (int32_t)((hi - lo + kSpanBytes - 1) / kSpanBytes);
+        a.range_bytes = hi - lo;
     } else {
         a.groups = (a.c_hi - a.c_lo + p.chunks_per_group - 1) / p.chunks_per_group;
+        a.range_bytes = (a.c_hi - a.c_lo) * p.chunk_bytes;
     }
     return a;
 }
@@ -1134,25 +1138,14 @@ CopyArgs copy_args(const CopyPlan& p, uint8_t* cache, int64_t cache_blocks, int3
 // Most workgroups of a launch, by its work-items.
 int64_t work_item_limit(int32_t threads) { return (1ll << 31) / threads; }
 
-// Workgroups of a scatter of at most `bound` units, `groups` a block. The host
-// does not know how few blocks were created, and each workgroup with nothing
-// to move costs about 0.6 ns; too few that loop cost a dense scatter up to 4
-// %. An insert mostly creates a few blocks a request, so the grid follows
-// what a block is worth (one round of the device per unit of a block: 149
-// blocks of 128 KiB, with their insert, 58.8 us at 8,192 workgroups, 54.8 at
-// 2,048) and what the call could move at all, up to 8,192 (1,024 blocks of 2
-// MiB: 815 us; at 4,096 822, at 2,048 835, at 512 854).
-int64_t loop_grid(const CopyPlan& p, int32_t groups, int64_t bound) {
-    const int64_t round = p.loop_grid / 16;
-    int64_t g = round * groups < bound / 4 ? round * groups : bound / 4;
-    if (g < round) g = round;
-    return g < p.loop_grid ? g : p.loop_grid;
-}
-
-// Workgroups of a copy of at most `bound` units, `groups` a block.
-int64_t copy_grid(const CopyPlan& p, bool gather, int32_t threads, int32_t groups, int64_t bound) {
+// Workgroups of a copy of up to `entries` blocks with the plan's grid or a
+// gather's; a scatter's follows scatter_grid.
+int64_t copy_grid(const CopyPlan& p, const CopyArgs& a, bool gather, int32_t threads) {
+    const int64_t bound = a.entries * a.groups;  // units if every entry moves
     const int64_t cap = work_item_limit(threads);
-    int64_t grid = p.grid ? p.grid : (gather ? (int64_t)p.gather_grid : loop_grid(p, groups, bound));
+    int64_t grid = p.grid ? p.grid
+                   : gather ? (int64_t)p.gather_grid
+                            : scatter_grid(p.loop_grid / 16, a.entries, a.groups, a.range_bytes);
     if (grid > bound) grid = bound;
     return grid < cap ? grid : cap;
 }
@@ -1166,9 +1159,8 @@ hipError_t copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache, int64_
     a.dests = sc.dests;
     a.total = GATHER ? sc.nslices : sc.total;  // a gather has at most one slice per entry
     a.entries = (int64_t)R * max_blocks;
-    const int64_t bound = a.entries * a.groups;  // units if every entry moves
     const int32_t threads = GATHER ? p.gather_threads : p.threads;
-    int64_t grid = copy_grid(p, GATHER, threads, a.groups, bound);
+    int64_t grid = copy_grid(p, a, GATHER, threads);
     if (grid < 1) return hipSuccess;
     if (p.tier.host_blocks > 0) {
         // a small looping grid for the host link, whose workgroups start
@@ -1176,6 +1168,7 @@ hipError_t copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache, int64_
         // (of this call or of calls on other streams)
         a.first_h = sc.total;
         a.total_h = GATHER ? sc.nslices_h : sc.total_h;
+        const int64_t bound = a.entries * a.groups;
         a.host_wgs = (int32_t)(bound < p.host_grid ? bound : p.host_grid);
         const int64_t room = work_item_limit(threads) - a.host_wgs;
         grid = (grid < room ? grid : room) + a.host_wgs;
@@ -1299,7 +1292,7 @@ hipError_t launch_gather_one(const CopyPlan& p, const int32_t* ids, const int32_
     a.m = m;
     a.state = p.state;
     a.entries = max_blocks;
-    const int64_t grid = copy_grid(p, true, p.threads, a.groups, a.entries * a.groups);
+    const int64_t grid = copy_grid(p, a, true, p.threads);
     if (grid < 1) return hipSuccess;
     if (p.lbase)
         hipLaunchKernelGGL(k_copy_entry_spans, dim3((unsigned)grid), dim3(p.threads), 0, s, a);
