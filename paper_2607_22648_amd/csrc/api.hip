@@ -744,7 +744,6 @@ int ptstore_gather_layers(ptstore_t* s, const int32_t* ids, const int32_t* m,
     rc = copy_scratch_for(s, st, R, max_blocks, &scr, &tcap, &ent, "ptstore_gather: scratch");
     if (rc) return rc;
     if (gathers_without_list(plan, R)) {
-        { Timed t(s, 4, st); }  // a selection of no kernels
         Timed t(s, 0, st);
         e = launch_gather_one(plan, ids, m, block_table, max_blocks, static_cast<uint8_t*>(cache),
                               cache_blocks, layer_begin, layer_end, st);
@@ -934,7 +933,7 @@ int ptstore_insert(ptstore_t* s, const int32_t* tokens, const int64_t* offsets, 
         Timed t(s, 3, st);
         const IndexView ix = index_view(s);
         e = launch_insert_match(ix, tgt, s->evs, b, sc, m_out, ids, created, st);
-        if (e == hipSuccess && s->evs.on) {
+        if (e == hipSuccess && s->evs.on && !evicts_in_rank(tgt.capacity)) {
             Timed te(s, 5, st);
             e = launch_evict(ix, tgt, s->evs, st);
         }

@@ -524,7 +524,6 @@ hipError_t launch_search(const EvictView& ev, DevState* st, int64_t n, int64_t c
 
 hipError_t launch_evict(const IndexView& ix, const InsertTarget& tgt, const EvictView& ev,
                         hipStream_t s) {
-    if (evicts_in_rank(tgt.capacity)) return hipSuccess;  // done by the insert's rank kernel
     hipError_t e = launch_search(ev, ix.state, tgt.capacity, tgt.capacity, ix.slot_mask + 1, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_ev_mark, dim3(grid_for(ev.words * kWave, 2048)), dim3(kThreads), 0, s, ev,

@@ -59,7 +59,7 @@ __device__ inline Slot empty_slot() {
     return z;
 }
 
-// A store of at most this many blocks evicts in one workgroup of 1024
+// A store of at most kSmallEvictMax blocks evicts in one workgroup of 1024
 // threads, 16 blocks each, their priorities and depths in registers: one
 // pass over memory and a few LDS digit passes of about 1 us, where the
 // kernels for larger stores cost a launch each. An insert of 128 chat turns
@@ -69,8 +69,7 @@ __device__ inline Slot empty_slot() {
 // (about 0.1 TB/s) starts to show.
 constexpr int kSmallEvictPer = 16;
 constexpr int kSmallEvictThreads = 1024;
-constexpr int64_t kSmallEvictMax = (int64_t)kSmallEvictPer * kSmallEvictThreads;
-inline bool evicts_in_rank(int64_t capacity) { return capacity <= kSmallEvictMax; }
+static_assert(kSmallEvictMax == (int64_t)kSmallEvictPer * kSmallEvictThreads, "blocks of the workgroup");
 
 // The digit of a 2048-bin histogram whose bin holds the need-th smallest key
 // (need >= 1, at most the keys counted); *before: keys in smaller bins. All
