@@ -1,5 +1,5 @@
-"""Block sizes that are multiples of four: their windows pass through LDS in parts of sixteen
-tokens. Against the CPU oracle, bit-exact."""
+"""Block sizes by the way their windows are read: sixteen tokens, other multiples of four (through
+LDS in parts of sixteen tokens), any other size. Against the CPU oracle, bit-exact."""
 from __future__ import annotations
 
 import numpy as np
@@ -13,8 +13,8 @@ if torch.cuda.is_available():
 
 
 @pytest.mark.parametrize("maxb", [7, 64, 130, 300])
-@pytest.mark.parametrize("bt", [4, 8, 12, 16, 20, 32, 36, 60, 64])
-def test_windows_of_fours(bt, maxb):
+@pytest.mark.parametrize("bt", [4, 8, 12, 16, 20, 32, 36, 60, 64, 5, 63])
+def test_windows_of_any_block(bt, maxb):
     """Requests that start on any token, end inside a block or between two, share prefixes of
     every length (window edges among them) and differ in the first, a middle or the last token
     of one block only; one request has no whole block, one is empty."""

@@ -33,8 +33,8 @@ def test_one_request_of_any_entries(slabs, m):
     ids[0, 8::19] = -1
     ids[0, 9::23] = cap
     ms = np.array([m], dtype=np.int32)
-    for grid, layers in ((0, None), (3, None), (0, (1, 4))):
-        if grid:
+    for grid, layers in ((0, None), (0, (1, 4)), (3, None), (3, (1, 4))):
+        if grid:  # stays set: the default grid comes first
             t.gpu.set_copy_shape(grid=grid)
         b0, r0 = t.gpu.stats()["bad_entries"], t.ref.bad_entries
         dst = torch.full((NB * t.shape.block_bytes,), 0x5A, dtype=torch.uint8, device=DEV)

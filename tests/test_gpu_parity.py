@@ -125,7 +125,7 @@ def test_one_request_blocks_sharing_a_batch_entry(weak_hash):
     t.close()
 
 
-@pytest.mark.parametrize("bt", [4, 16])
+@pytest.mark.parametrize("bt", [4, 5, 16])
 @pytest.mark.parametrize("maxb", [130, 300, 700])
 def test_weak_hash_long_requests(maxb, bt):
     """Key collisions in requests of several windows, looked up a workgroup
@@ -135,8 +135,9 @@ def test_weak_hash_long_requests(maxb, bt):
     other tokens, or the right tokens under another parent; either way the
     lane probes on, at any lane of a window, and the result is the
     sequential one. 16-token blocks take the kernels' LDS-staged path, with
-    stored rows compared four lanes to a row; 4-token blocks the generic
-    one."""
+    stored rows compared four lanes to a row; 4-token blocks the one of any
+    multiple of four, which passes through LDS in parts; 5-token blocks the
+    generic one, where each lane reads its own block."""
     rng = np.random.default_rng(maxb + bt)
     atoms = _atoms(rng, 3, bt, 3)
     t = Twin(1, 1, 8, bt, 100_000, flags=P.PTSTORE_FLAG_WEAK_HASH | P.PTSTORE_FLAG_COUNTERS)
