@@ -1083,10 +1083,13 @@ hipError_t select(const CopyPlan& p, const CopyScratch& sc, const int32_t* ids, 
         return hipGetLastError();
     }
     if ((int64_t)R * max_blocks <= kSmallMaxEntries) {
-        if (a.group)
-            hipLaunchKernelGGL((k_select_small<GATHER, true>), dim3(1), dim3(kSmallThreads), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_select_small<GATHER, false>), dim3(1), dim3(kSmallThreads), 0, s, a);
+        if constexpr (GATHER) {  // a scatter does not group
+            if (a.group) {
+                hipLaunchKernelGGL((k_select_small<true, true>), dim3(1), dim3(kSmallThreads), 0, s, a);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((k_select_small<GATHER, false>), dim3(1), dim3(kSmallThreads), 0, s, a);
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)((R + kSelWaves - 1) / kSelWaves);
