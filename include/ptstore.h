@@ -242,7 +242,9 @@ int ptstore_lookup(ptstore_t *store, const int32_t *tokens, const int64_t *offse
  * request, grown on demand; growing waits for `stream`), then copies only
  * those blocks. With R >= 2 the list groups the entries by stored block, so
  * that a block several requests need is read once per call and written to
- * each of their cache blocks. Blocks read from device memory are copied on
+ * each of their cache blocks. With R == 1 and no host tier the copy walks the
+ * request's entries itself and no list is built (the scratch is made all the
+ * same, so that what a later call finds does not depend on it). Blocks read from device memory are copied on
  * the full device, blocks read from the host tier by a quarter of the
  * compute units (they move at the host link's rate whatever the grid, and
  * the rest of the device stays free for device-memory copies, of this call
@@ -502,11 +504,15 @@ int ptstore_kernel_times(ptstore_t *store, int32_t kind, double *total_ms, int64
  * default the smallest divisor of 2 * num_layers that leaves at most 64
  * units per block, and a gather of a layer range of at most 4 chunks per
  * block moves the whole range as one unit; once set here, it applies to
- * every copy); threads: workgroup size, 64..1024, a multiple of 64
- * (default 1024); grid: workgroups of the copy kernels (by default a
- * gather launches one per possible unit, up to 512 times the workgroups
- * the device holds at once, and a scatter 16 times the workgroups the
- * device holds, looping; a grid once set replaces both until set again).
+ * every copy); threads: workgroup size, 64..1024, a multiple of 64 (default
+ * 1024, and 512 for a gather of several requests that moves one chunk per
+ * unit and has no per-layer slab sizes; once set here, it applies to every
+ * copy); grid: workgroups of the copy kernels. By default a gather launches
+ * one per possible unit, up to 512 times the 1024-thread workgroups the
+ * device holds at once, and a scatter, whose workgroups loop, 4 to 16 times
+ * as many as the device holds, by the bytes a block and the call are worth;
+ * a grid once set replaces both until set again. Host-tier rows have
+ * workgroups of their own, a quarter as many as compute units, in every case.
  * For tuning sweeps; results never depend on it. */
 int ptstore_set_copy_shape(ptstore_t *store, int32_t chunks_per_group, int32_t threads,
                            int32_t grid);

@@ -209,26 +209,31 @@ CopyPlan copy_plan(ptstore_t* s) {
     p.chunks_per_group = s->chunks_per_group;
     p.threads = s->threads;
     p.grid = s->grid;
-    // in rounds of the workgroups the device holds at once (2048 threads per
-    // compute unit): a gather launches one workgroup per possible unit, up to
-    // 512 rounds, past which a workgroup takes further units a grid apart.
+    // in rounds of the 1,024-thread workgroups the device holds at once (2048
+    // threads per compute unit): a gather launches one workgroup per possible
+    // unit, up to 512 rounds (262,144 workgroups on 256 compute units; 256
+    // rounds of the 512-thread ones below), past which a workgroup takes
+    // further units a grid apart.
     // The host cannot know how many units a call has: entries that miss, and
     // entries that share a row with others, leave possible units empty, and
     // each empty workgroup still costs its launch (about 0.8 ns). On the
     // trie's 8,192 walks, whose 517,672 entries read 70,570 rows (184,474
     // units of 1,048,576 possible), 512 rounds copy in 7.46 ms against 8.11
     // at 2,048 rounds and 7.42 with exactly one workgroup per unit; on the 8B
-    // shape (759,808 units) 12.38 against 12.47 and 12.21. A scatter, whose units are
-    // sparse, launches at most 16 rounds that loop (4 rounds: 7 % slower on a
-    // large scatter; 128 rounds: 45 % slower on a small one).
+    // shape (759,808 units) 12.38 against 12.47 and 12.21 (1,024 threads). A
+    // scatter, whose units are sparse, launches 4 to 16 rounds that loop (see
+    // scatter_grid).
     const int resident = s->cus * (2048 / s->threads);
     // A gather of uniform slabs, one chunk per unit, runs in workgroups of 512
     // threads: an empty one costs about half as much to launch, and four of
     // them on a compute unit even out better than two. 64 requests on a
-    // 2-layer model (16,384 possible units, 2,700 real) 115 -> 107 us, 4,096
-    // walks of one-layer blocks 3,940 -> 3,825, 48 requests on the 8B shape
-    // 6,021 / 6,031. Several chunks per unit (70B shape, layer ranges) and
-    // spans of per-layer slabs measured the same or slower than at 1,024.
+    // 2-layer model (16,384 possible units, 2,700 real) take 106 us, at 1,024
+    // threads 114. Large calls do not tell the two apart: 1,024 threads take
+    // 0.998 +- 0.032 times as long on 4,096 walks of one-layer blocks and 1.013
+    // +- 0.027 on 48 requests on the 8B shape, where the spread comes from where
+    // the pool lands in memory. Several chunks per unit (70B shape, layer
+    // ranges) and spans of per-layer slabs measured the same or slower than at
+    // 1,024.
     p.gather_threads = s->threads_set || s->layer_tab || s->chunks_per_group > 1 ? s->threads : 512;
     p.gather_grid = resident * 512;
     p.loop_grid = resident * 16;

@@ -40,9 +40,9 @@
 // the [request][block] arrays (a few created blocks per insert, half the
 // requests missing the store). The default copy shape gives each
 // workgroup one chunk per unit: four vectors per thread of a 32 KiB chunk in a
-// gather of several requests (512 threads), two in any other call (1024). The copies are pure HBM streaming: no MFMA. LDS holds the
-// row tables of the grouping step and the per-layer kernel's table of layer
-// bases.
+// gather of several requests (512 threads), two in any other call (1024). The
+// copies are pure HBM streaming: no MFMA. LDS holds the row tables of the
+// grouping step and the per-layer kernel's table of layer bases.
 #include "kernels.hpp"
 #include "launch_rules.hpp"
 
@@ -672,8 +672,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_slices(SelectArgs a) {
 // that each knows where the created blocks come in the list, and writes its
 // share of it. An entry out of range keeps its place with row -1. Counting,
 // scanning and filling had been three launches of about 4.6 us around 1 us
-// of work; the pass of 128 chat turns that create 149 blocks went from 65.8
-// to 59.3 us. (Copying straight from the flags, with no list, takes 3 us less
+// of work; the pass of 128 chat turns that create 149 blocks takes 52.9 us, by
+// the three launches 59.0. (Copying straight from the flags, with no list, takes 3 us less
 // here but 3 to 15 % more where many blocks are created: its workgroups have
 // to be few, and the device then waits for the slowest.)
 constexpr int kFlagsThreads = 1024;
@@ -787,7 +787,7 @@ struct CopyArgs {
 // bounds, and all others those of device rows at the same time: one after
 // the other, in two launches, the device rows' copy had come on top (a
 // request pair of which 72 of 960 blocks of 5 MiB lie in host memory: 8.40
-// ms in two launches, 6.70 in one).
+// ms in two launches, 6.69 in one).
 struct Share {
     unsigned long long first, total;  // descriptors
     unsigned long long wg, wgs;       // this workgroup among those of the part
@@ -867,8 +867,8 @@ __device__ inline int32_t slice_dests(const CopyArgs& a, const Slice& q) {
 // order (its ids are a path), without a host tier. It needs no list: the
 // descriptors are the request's own entries, each checked here as the
 // selection would; a bad one is counted by its first unit. A lookup and
-// gather of 48 blocks of 128 KiB takes 15.8 us so, 19.5 with the selection's
-// launch between them; of 175 blocks of 2 MiB 143 instead of 150.
+// gather of 48 blocks of 128 KiB takes 15.6 us so, 18.9 with the selection's
+// launch between them; of 175 blocks of 2 MiB 143 instead of 149.
 template <bool ENTRIES>
 __device__ inline void copy_slices(const CopyArgs& a) {
     const Share h = ENTRIES ? Share{0, 0, blockIdx.x, gridDim.x} : share_of(a);

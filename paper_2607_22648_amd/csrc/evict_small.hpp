@@ -63,9 +63,8 @@ __device__ inline Slot empty_slot() {
 // threads, 16 blocks each, their priorities and depths in registers: one
 // pass over memory and a few LDS digit passes of about 1 us, where the
 // kernels for larger stores cost a launch each. An insert of 128 chat turns
-// and its (payload-free) scatter into a full store takes 62 us with 5,120
-// blocks and 72 with 16,336; by the kernels of evict.hip 103 and 105. Past
-// 16 blocks a thread the registers run out, and one compute unit's bandwidth
+// and its scatter into a full store takes 55 us with 5,120 blocks and 63 with
+// 16,336; by the kernels of evict.hip 99 and 98. Past 16 blocks a thread the registers run out, and one compute unit's bandwidth
 // (about 0.1 TB/s) starts to show.
 constexpr int kSmallEvictPer = 16;
 constexpr int kSmallEvictThreads = 1024;
