@@ -64,8 +64,9 @@ __device__ inline Slot empty_slot() {
 // pass over memory and a few LDS digit passes of about 1 us, where the
 // kernels for larger stores cost a launch each. An insert of 128 chat turns
 // and its scatter into a full store takes 55 us with 5,120 blocks and 63 with
-// 16,336; by the kernels of evict.hip 99 and 98. Past 16 blocks a thread the registers run out, and one compute unit's bandwidth
-// (about 0.1 TB/s) starts to show.
+// 16,336; by the kernels of evict.hip 99 and 98. Past 16 blocks a thread the
+// registers run out, and one compute unit's bandwidth (about 0.1 TB/s) starts
+// to show.
 constexpr int kSmallEvictPer = 16;
 constexpr int kSmallEvictThreads = 1024;
 static_assert(kSmallEvictMax == (int64_t)kSmallEvictPer * kSmallEvictThreads, "blocks of the workgroup");
