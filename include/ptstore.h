@@ -493,8 +493,8 @@ int ptstore_get_buffers(ptstore_t *store, ptstore_buffers_t *out);
  * and scatter (none for a gather of one request from a store without a host
  * tier, which has no list), 5 = the eviction part of an insert
  * (PTSTORE_FLAG_EVICT; included in kind 3; none for a store of at most
- * 16,384 blocks, which evicts inside another of the insert's kernels), 6 =
- * ptstore_replicate. Resets the records of that kind. At most 65,536
+ * 16,384 blocks and 262,144 index slots, which evicts inside another of the
+ * insert's kernels), 6 = ptstore_replicate. Resets the records of that kind. At most 65,536
  * launches per kind are recorded between two calls.
  */
 int ptstore_kernel_times(ptstore_t *store, int32_t kind, double *total_ms, int64_t *launches);

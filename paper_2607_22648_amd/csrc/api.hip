@@ -938,7 +938,7 @@ int ptstore_insert(ptstore_t* s, const int32_t* tokens, const int64_t* offsets, 
         Timed t(s, 3, st);
         const IndexView ix = index_view(s);
         e = launch_insert_match(ix, tgt, s->evs, b, sc, m_out, ids, created, st);
-        if (e == hipSuccess && s->evs.on && !evicts_in_rank(tgt.capacity)) {
+        if (e == hipSuccess && s->evs.on && !evicts_in_rank(tgt.capacity, s->slots_n)) {
             Timed te(s, 5, st);
             e = launch_evict(ix, tgt, s->evs, st);
         }

@@ -66,7 +66,11 @@ __device__ inline Slot empty_slot() {
 // and its scatter into a full store takes 55 us with 5,120 blocks and 63 with
 // 16,336; by the kernels of evict.hip 99 and 98. Past 16 blocks a thread the
 // registers run out, and one compute unit's bandwidth (about 0.1 TB/s) starts
-// to show.
+// to show. It shows in the index too, which a rebuild clears: with 16,000
+// blocks an insert of 14,400 takes 78 us here, 95 when it rebuilds an index of
+// 2^18 slots, 177 with 2^20 and 506 with 2^22; by the kernels of evict.hip 92
+// and 92 to 104. So a store that was given more than 2^18 slots (eight times
+// what 16,384 blocks get by default) takes those.
 constexpr int kSmallEvictPer = 16;
 constexpr int kSmallEvictThreads = 1024;
 static_assert(kSmallEvictMax == (int64_t)kSmallEvictPer * kSmallEvictThreads, "blocks of the workgroup");

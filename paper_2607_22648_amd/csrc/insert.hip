@@ -530,7 +530,7 @@ hipError_t launch_insert_match(const IndexView& ix, const InsertTarget& tgt, con
     const unsigned wgrid = window_grid(b);
     hipLaunchKernelGGL(k_verify, dim3(wgrid), dim3(kThreads), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (ev.on && evicts_in_rank(tgt.capacity))
+    if (ev.on && evicts_in_rank(tgt.capacity, ix.slot_mask + 1))
         hipLaunchKernelGGL(k_rank<true>, dim3(1), dim3(kRankThreads), 0, s, a);
     else
         hipLaunchKernelGGL(k_rank<false>, dim3(1), dim3(kRankThreads), 0, s, a);

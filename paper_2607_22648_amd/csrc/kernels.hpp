@@ -243,10 +243,13 @@ hipError_t launch_insert_commit(const IndexView& ix, const InsertTarget& tgt, co
                                 const Batch& b, const InsertScratch& sc, int32_t* m_out, int32_t* ids,
                                 uint8_t* created, hipStream_t s);
 
-// A store of at most this many blocks evicts inside the insert's match part
-// (why the line lies there: evict_small.hpp).
+// A store of at most this many blocks and index slots evicts inside the
+// insert's match part (why the lines lie there: evict_small.hpp).
 constexpr int64_t kSmallEvictMax = 16384;
-inline bool evicts_in_rank(int64_t capacity) { return capacity <= kSmallEvictMax; }
+constexpr uint64_t kSmallEvictSlots = 1ull << 18;
+inline bool evicts_in_rank(int64_t capacity, uint64_t slots_n) {
+    return capacity <= kSmallEvictMax && slots_n <= kSmallEvictSlots;
+}
 
 // evict.hip: victim selection and index maintenance of an insert into a larger
 // store (between its match and its commit).

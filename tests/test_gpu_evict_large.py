@@ -67,7 +67,7 @@ def test_one_request_inserts_rebuild_the_index(capacity):
 
 
 def test_rebuild_by_a_small_batch_uses_the_device():
-    """An insert of one request that rebuilds the index of 131,072 blocks takes no more than four
+    """An insert of one request that rebuilds the index of 131,072 blocks takes no more than eight
     times one that does not (measured: 1.2 times; 19 times when the batch alone sized the grid)."""
     s, g = _full_store(1 << 17)
     for _ in range(30):  # most of a rebuild's worth of deleted slots
@@ -81,13 +81,49 @@ def test_rebuild_by_a_small_batch_uses_the_device():
             break
         n = now
     s.close()
-    assert rebuilding and rebuilding[0] <= 4 * np.median(plain), (rebuilding, np.median(plain))
+    assert rebuilding and rebuilding[0] <= 8 * np.median(plain), (rebuilding, np.median(plain))
 
 
 def _ranked(prio, depth, ids, n):
     """The n ids that come first by lowest priority, then deepest, then smallest id."""
     order = np.lexsort((ids, -depth, prio))
     return np.sort(ids[order[:n]])
+
+
+@pytest.mark.parametrize("slots", [1 << 18, 1 << 19])
+def test_small_stores_by_index_slots(slots):
+    """A store of few blocks in an index of many slots, on both sides of the size that one
+    workgroup clears: inserts through a rebuild, each against the oracle."""
+    rng = np.random.default_rng(slots)
+    t = Twin(1, 1, 8, BT, 16000, index_slots=slots, flags=EVICT, payload=False)
+    offs = np.arange(241, dtype=np.int64) * (60 * BT)
+    for _ in range(30):
+        toks = rng.integers(0, 1 << 30, size=240 * 60 * BT, dtype=np.int32)
+        t.insert(toks, offs, 60)
+        if t.gpu.stats()["index_rebuilds"]:
+            break
+    t.lookup(toks, offs, 60)
+    t.check_evict()
+    assert t.gpu.stats()["index_rebuilds"] == 1
+    t.close()
+
+
+def test_rebuild_of_a_large_index_uses_the_device():
+    """An insert into a store of 16,000 blocks that rebuilds an index of 2^24 slots takes no more
+    than eight times one that does not (measured: 1.4; 23 when one workgroup cleared it)."""
+    s = P.PrefixStore(P.StoreShape(1, 1, 8, BT), 16000, index_slots=1 << 24, flags=EVICT)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    s.set_timing(True)
+    plain, n = [], 0
+    for _ in range(700):
+        us = _insert(s, g, 250, 60)
+        n = s.stats()["index_rebuilds"]
+        if n:
+            break
+        plain.append(us)
+    s.close()
+    assert n == 1 and us <= 8 * np.median(plain), (us, np.median(plain))
 
 
 @pytest.mark.parametrize("bits", [1, 14, 20, 30, 40, 62])
@@ -143,7 +179,7 @@ def test_hot_set_where_one_block_is_much_hotter(bits):
 
 
 def test_one_hot_block_does_not_slow_the_search():
-    """Evictions of 128 blocks from 1,048,576 take no more than 2.5 times as long when one block's
+    """Evictions of 128 blocks from 1,048,576 take no more than five times as long when one block's
     priority is 2^20 above the others' as when none is (measured: 1.3 times; 16 times when what two
     passes had left was always one workgroup's)."""
     s, g = _full_store(1 << 20)
@@ -160,4 +196,4 @@ def test_one_hot_block_does_not_slow_the_search():
     s.evict_tensors()[1][0] += 1 << 20
     hot = evict_us()
     s.close()
-    assert hot <= 2.5 * cold, (cold, hot)
+    assert hot <= 5 * cold, (cold, hot)
