@@ -808,6 +808,13 @@ __device__ inline Share share_of(const CopyArgs& a) {
     return h;
 }
 
+// The same of a gather of one request without a list: its first m entries,
+// walked by the whole grid.
+__device__ inline Share share_of_entries(const CopyArgs& a) {
+    const int64_t m = *a.m;
+    return Share{0, (unsigned long long)max(min(m, a.entries), (int64_t)0), blockIdx.x, gridDim.x};
+}
+
 // Unit number -> descriptor. Nearly every call has fewer than 2^32 possible
 // units; a 64-bit division is several times as long.
 __device__ inline unsigned long long unit_desc(unsigned long long unit, int groups) {
@@ -871,9 +878,8 @@ __device__ inline int32_t slice_dests(const CopyArgs& a, const Slice& q) {
 // launch between them; of 175 blocks of 2 MiB 143 instead of 149.
 template <bool ENTRIES>
 __device__ inline void copy_slices(const CopyArgs& a) {
-    const Share h = ENTRIES ? Share{0, 0, blockIdx.x, gridDim.x} : share_of(a);
-    const unsigned long long units = (ENTRIES ? (unsigned long long)a.entries : h.total) *
-                                     (unsigned long long)a.groups;
+    const Share h = ENTRIES ? share_of_entries(a) : share_of(a);
+    const unsigned long long units = h.total * (unsigned long long)a.groups;
     const int n16 = (int)(a.chunk_bytes >> 4);
     const int nt = blockDim.x;
     for (unsigned long long unit = h.wg; unit < units; unit += h.wgs) {
@@ -882,10 +888,9 @@ __device__ inline void copy_slices(const CopyArgs& a) {
         Slice q;
         int32_t lane_cb;
         if (ENTRIES) {
-            // every load before any test (d is inside the arrays): one trip
-            const int32_t m = *a.m, id = a.ids[d], cb = a.table[d];
+            // every load before any test: one trip
+            const int32_t id = a.ids[d], cb = a.table[d];
             const unsigned long long count = a.state->count;
-            if ((int64_t)d >= (int64_t)m) break;
             if (cb < 0) continue;
             if ((int64_t)cb >= a.cache_blocks || id < 0 || (unsigned long long)id >= count) {
                 if (g == 0 && threadIdx.x == 0) atomicAdd(&a.state->bad_entries, 1ull);
@@ -969,9 +974,7 @@ template <bool GATHER, bool ENTRIES>
 __device__ inline void copy_spans(const CopyArgs& a) {
     __shared__ int64_t lb[kMaxVarLayers + 1];
     const unsigned long long spans = (unsigned)a.groups;  // kSpanBytes units per descriptor
-    const Share h = ENTRIES ? Share{0, (unsigned long long)max(min((int64_t)*a.m, a.entries), (int64_t)0),
-                                    blockIdx.x, gridDim.x}
-                            : share_of(a);
+    const Share h = ENTRIES ? share_of_entries(a) : share_of(a);
     const unsigned long long units = h.total * spans, first = h.first;
     if (h.wg >= units) return;  // the whole workgroup: nothing to move
     const int l0 = a.c_lo >> 1, l1 = a.c_hi >> 1, nl = l1 - l0;
