@@ -58,9 +58,10 @@ constexpr int kSelWaves = kSelThreads / kWave;
 __device__ inline v4u ld_nt(const v4u* p) { return __builtin_nontemporal_load(p); }
 __device__ inline void st_nt(v4u* p, v4u v) { __builtin_nontemporal_store(v, p); }
 
-// Copy n16 16-byte vectors with blockDim.x threads.
-__device__ inline void copy_span(const v4u* __restrict__ src, v4u* __restrict__ dst, int n16) {
-    const int nt = blockDim.x;
+// Copy n16 16-byte vectors with the workgroup's nt threads. (The copies take
+// their workgroup size from the arguments: blockDim.x is a memory load, and the
+// compiler is free to put it inside the loop over units.)
+__device__ inline void copy_span(const v4u* __restrict__ src, v4u* __restrict__ dst, int n16, int nt) {
     int i = threadIdx.x;
     for (; i + (kUnroll - 1) * nt < n16; i += kUnroll * nt) {
         v4u v[kUnroll];
@@ -771,6 +772,7 @@ struct CopyArgs {
     const unsigned long long* first_h;  // the first descriptor of a host-tier row
     const unsigned long long* total_h;  // descriptors from there
     int32_t host_wgs;                   // workgroups that copy host-tier rows (0: no host tier)
+    int32_t threads;                    // of a workgroup
     int64_t block_bytes;
     int64_t chunk_bytes;
     int64_t cache_blocks;
@@ -792,27 +794,39 @@ struct Share {
     unsigned long long first, total;  // descriptors
     unsigned long long wg, wgs;       // this workgroup among those of the part
 };
+// What a copy walks. Kernels of their own, since the choice at run time costs
+// every workgroup a further trip for its arguments before it knows whether it
+// has a unit at all, and most of a sparse call's have none (one layer of 512
+// requests with one block each, 32,768 possible units: 89.4 us with the choice
+// in the kernel, 86.7 without).
+enum Walk {
+    kList,        // descriptors of device rows
+    kTieredList,  // of a store with a host tier: both parts
+    kEntries,     // the first m entries of one request, without a list
+};
+template <int WALK>
 __device__ inline Share share_of(const CopyArgs& a) {
     Share h;
-    if ((int)blockIdx.x < a.host_wgs) {
-        h.first = *a.first_h;
-        h.total = *a.total_h;
-        h.wg = blockIdx.x;
-        h.wgs = (unsigned)a.host_wgs;
-    } else {
-        h.first = 0;
-        h.total = *a.total;
-        h.wg = blockIdx.x - (unsigned)a.host_wgs;
-        h.wgs = gridDim.x - (unsigned)a.host_wgs;
+    h.first = 0;
+    h.wg = blockIdx.x;
+    h.wgs = gridDim.x;
+    if (WALK == kEntries) {
+        const int64_t m = *a.m;
+        h.total = (unsigned long long)max(min(m, a.entries), (int64_t)0);
+        return h;
     }
+    if (WALK == kTieredList) {
+        if ((int)blockIdx.x < a.host_wgs) {
+            h.first = *a.first_h;
+            h.total = *a.total_h;
+            h.wgs = (unsigned)a.host_wgs;
+            return h;
+        }
+        h.wg -= (unsigned)a.host_wgs;
+        h.wgs -= (unsigned)a.host_wgs;
+    }
+    h.total = *a.total;
     return h;
-}
-
-// The same of a gather of one request without a list: its first m entries,
-// walked by the whole grid.
-__device__ inline Share share_of_entries(const CopyArgs& a) {
-    const int64_t m = *a.m;
-    return Share{0, (unsigned long long)max(min(m, a.entries), (int64_t)0), blockIdx.x, gridDim.x};
 }
 
 // Unit number -> descriptor. Nearly every call has fewer than 2^32 possible
@@ -830,14 +844,24 @@ __device__ inline unsigned long long unit_desc(unsigned long long unit, int grou
 // and workgroups past the end exit at once); a scatter, whose created blocks
 // are sparse, launches a looping grid (scatter_grid).
 // Scatter, uniform slabs: a unit is (pair, group of chunks_per_group slabs).
-__global__ __launch_bounds__(1024) void k_copy_pairs(CopyArgs a) {
-    const Share h = share_of(a);
+template <int WALK>
+__device__ inline void copy_pairs(const CopyArgs& a) {
+    const Share h = share_of<WALK>(a);
     const unsigned long long units = h.total * (unsigned long long)a.groups;
+    if (h.wg >= units) return;
     const Pair* pairs = a.pairs + h.first;
     const int n16 = (int)(a.chunk_bytes >> 4);
-    for (unsigned long long unit = h.wg; unit < units; unit += h.wgs) {
-        const unsigned long long d = unit_desc(unit, a.groups);
-        const int g = (int)(unit - d * (unsigned)a.groups);
+    // the loop steps by whole descriptors and groups: a division per unit
+    // shows where a unit is a few KiB
+    unsigned long long d = unit_desc(h.wg, a.groups);
+    int g = (int)(h.wg - d * (unsigned)a.groups);
+    const unsigned step_d = (unsigned)h.wgs / (unsigned)a.groups;
+    const int step_g = (int)((unsigned)h.wgs - step_d * (unsigned)a.groups);
+    for (unsigned long long unit = h.wg; unit < units; unit += h.wgs, d += step_d, g += step_g) {
+        if (g >= a.groups) {
+            g -= a.groups;
+            ++d;
+        }
         const Pair p = pairs[d];
         if (p.row < 0) continue;  // an entry out of range
         const int c0 = a.c_lo + g * a.chunks_per_group;
@@ -847,10 +871,13 @@ __global__ __launch_bounds__(1024) void k_copy_pairs(CopyArgs a) {
         for (int c = c0; c < c1; ++c) {
             uint8_t* row_chunk = blk + (int64_t)c * a.chunk_bytes;
             const uint8_t* cache_chunk = a.cache + ((int64_t)c * a.cache_blocks + p.cb) * a.chunk_bytes;
-            copy_span(reinterpret_cast<const v4u*>(cache_chunk), reinterpret_cast<v4u*>(row_chunk), n16);
+            copy_span(reinterpret_cast<const v4u*>(cache_chunk), reinterpret_cast<v4u*>(row_chunk), n16, a.threads);
         }
     }
 }
+
+__global__ __launch_bounds__(1024) void k_copy_pairs(CopyArgs a) { copy_pairs<kList>(a); }
+__global__ __launch_bounds__(1024) void k_copy_pairs_tiered(CopyArgs a) { copy_pairs<kTieredList>(a); }
 
 // A slice's cache blocks, one per lane (lane k holds the k-th; a slice has
 // at most kSliceDests <= kWave of them), loaded once per unit. The copy
@@ -870,24 +897,27 @@ __device__ inline int32_t slice_dests(const CopyArgs& a, const Slice& q) {
 // written to each of the slice's cache blocks: a row that several requests
 // need crosses the memory bus once per kSliceDests of them.
 //
-// ENTRIES: a call of one request, which reads each row once whatever its
+// kEntries: a call of one request, which reads each row once whatever its
 // order (its ids are a path), without a host tier. It needs no list: the
 // descriptors are the request's own entries, each checked here as the
 // selection would; a bad one is counted by its first unit. A lookup and
 // gather of 48 blocks of 128 KiB takes 15.6 us so, 18.9 with the selection's
-// launch between them; of 175 blocks of 2 MiB 143 instead of 149.
-template <bool ENTRIES>
+// launch between them; of 175 blocks of 2 MiB 143 instead of 149. A workgroup
+// reads m first and leaves if its unit lies past it: one block of 2 MiB of 2,048
+// possible (131,072 workgroups) takes 112 us so, 238 when every workgroup also
+// waited for an entry, 118 with the list.
+template <int WALK>
 __device__ inline void copy_slices(const CopyArgs& a) {
-    const Share h = ENTRIES ? share_of_entries(a) : share_of(a);
+    const Share h = share_of<WALK>(a);
     const unsigned long long units = h.total * (unsigned long long)a.groups;
     const int n16 = (int)(a.chunk_bytes >> 4);
-    const int nt = blockDim.x;
+    const int nt = a.threads;
     for (unsigned long long unit = h.wg; unit < units; unit += h.wgs) {
         const unsigned long long d = unit_desc(unit, a.groups);
         const int g = (int)(unit - d * (unsigned)a.groups);
         Slice q;
         int32_t lane_cb;
-        if (ENTRIES) {
+        if (WALK == kEntries) {
             // every load before any test: one trip
             const int32_t id = a.ids[d], cb = a.table[d];
             const unsigned long long count = a.state->count;
@@ -931,8 +961,9 @@ __device__ inline void copy_slices(const CopyArgs& a) {
     }
 }
 
-__global__ __launch_bounds__(1024) void k_copy_slices(CopyArgs a) { copy_slices<false>(a); }
-__global__ __launch_bounds__(1024) void k_copy_entries(CopyArgs a) { copy_slices<true>(a); }
+__global__ __launch_bounds__(1024) void k_copy_slices(CopyArgs a) { copy_slices<kList>(a); }
+__global__ __launch_bounds__(1024) void k_copy_slices_tiered(CopyArgs a) { copy_slices<kTieredList>(a); }
+__global__ __launch_bounds__(1024) void k_copy_entries(CopyArgs a) { copy_slices<kEntries>(a); }
 
 // Per-layer slab sizes. Layers l0 .. l1-1 of a pool row are one contiguous
 // byte range [lbase[l0], lbase[l1]); a unit is (descriptor, kSpanBytes of
@@ -970,24 +1001,24 @@ __device__ inline v4u* span_cache(const CopyArgs& a, const int64_t* lb, int li, 
 // A gather's unit is (slice, span): each vector of the row is read once
 // and written to each of the slice's cache blocks; a scatter's is (pair,
 // span).
-template <bool GATHER, bool ENTRIES>
+template <bool GATHER, int WALK>
 __device__ inline void copy_spans(const CopyArgs& a) {
     __shared__ int64_t lb[kMaxVarLayers + 1];
     const unsigned long long spans = (unsigned)a.groups;  // kSpanBytes units per descriptor
-    const Share h = ENTRIES ? share_of_entries(a) : share_of(a);
+    const Share h = share_of<WALK>(a);
     const unsigned long long units = h.total * spans, first = h.first;
     if (h.wg >= units) return;  // the whole workgroup: nothing to move
     const int l0 = a.c_lo >> 1, l1 = a.c_hi >> 1, nl = l1 - l0;
-    for (int l = l0 + (int)threadIdx.x; l <= l1; l += blockDim.x) lb[l - l0] = a.lbase[l];
+    for (int l = l0 + (int)threadIdx.x; l <= l1; l += a.threads) lb[l - l0] = a.lbase[l];
     __syncthreads();
     const int64_t b0 = lb[0], b1 = lb[nl];
-    const int64_t step = 16 * (int64_t)blockDim.x;
+    const int64_t step = 16 * (int64_t)a.threads;
     for (unsigned long long unit = h.wg; unit < units; unit += h.wgs) {
         const unsigned long long d = unit_desc(unit, a.groups);
         const int64_t s0 = b0 + (int64_t)(unit - d * spans) * kSpanBytes;
         const int64_t s1 = min(s0 + (int64_t)kSpanBytes, b1);
         int32_t row, n = 1, cb0 = 0, lane_cb = 0;
-        if (ENTRIES) {  // as in k_copy_slices
+        if (WALK == kEntries) {  // as in copy_slices
             const int32_t id = a.ids[d], cb = a.table[d];
             if (cb < 0) continue;
             if ((int64_t)cb >= a.cache_blocks || id < 0 || (unsigned long long)id >= a.state->count) {
@@ -1045,9 +1076,13 @@ __device__ inline void copy_spans(const CopyArgs& a) {
 
 template <bool GATHER>
 __global__ __launch_bounds__(1024) void k_copy_spans(CopyArgs a) {
-    copy_spans<GATHER, false>(a);
+    copy_spans<GATHER, kList>(a);
 }
-__global__ __launch_bounds__(1024) void k_copy_entry_spans(CopyArgs a) { copy_spans<true, true>(a); }
+template <bool GATHER>
+__global__ __launch_bounds__(1024) void k_copy_spans_tiered(CopyArgs a) {
+    copy_spans<GATHER, kTieredList>(a);
+}
+__global__ __launch_bounds__(1024) void k_copy_entry_spans(CopyArgs a) { copy_spans<true, kEntries>(a); }
 
 // Whole blocks from one row to another (replication): pairs[k].row is the
 // source row, pairs[k].cb the destination row; *total pairs. A block is
@@ -1067,7 +1102,7 @@ __global__ __launch_bounds__(1024) void k_copy_rows(CopyArgs a) {
         for (int k = 0; k < 2; ++k)
             blk[k] = rows[k] < a.dev_rows ? a.pool + rows[k] * a.block_bytes
                                           : a.host + (rows[k] - a.dev_rows) * a.block_bytes;
-        copy_span(reinterpret_cast<const v4u*>(blk[0] + off), reinterpret_cast<v4u*>(blk[1] + off), n16);
+        copy_span(reinterpret_cast<const v4u*>(blk[0] + off), reinterpret_cast<v4u*>(blk[1] + off), n16, a.threads);
     }
 }
 
@@ -1116,8 +1151,10 @@ hipError_t select(const CopyPlan& p, const CopyScratch& sc, const int32_t* ids, 
 }
 
 // What a copy of layers l0 .. l1-1 needs besides its descriptors.
-CopyArgs copy_args(const CopyPlan& p, uint8_t* cache, int64_t cache_blocks, int32_t l0, int32_t l1) {
+CopyArgs copy_args(const CopyPlan& p, uint8_t* cache, int64_t cache_blocks, int32_t threads, int32_t l0,
+                   int32_t l1) {
     CopyArgs a{};
+    a.threads = threads;
     a.pool = p.pool;
     a.host = p.tier.host;
     a.dev_rows = p.tier.dev_rows;
@@ -1159,13 +1196,13 @@ int64_t copy_grid(const CopyPlan& p, const CopyArgs& a, bool gather, int32_t thr
 template <bool GATHER>
 hipError_t copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache, int64_t cache_blocks,
                 int32_t R, int32_t max_blocks, int32_t l0, int32_t l1, hipStream_t s) {
-    CopyArgs a = copy_args(p, cache, cache_blocks, l0, l1);
+    const int32_t threads = GATHER ? p.gather_threads : p.threads;
+    CopyArgs a = copy_args(p, cache, cache_blocks, threads, l0, l1);
     a.pairs = sc.pairs;
     a.slices = sc.slices;
     a.dests = sc.dests;
     a.total = GATHER ? sc.nslices : sc.total;  // a gather has at most one slice per entry
     a.entries = (int64_t)R * max_blocks;
-    const int32_t threads = GATHER ? p.gather_threads : p.threads;
     int64_t grid = copy_grid(p, a, GATHER, threads);
     if (grid < 1) return hipSuccess;
     if (p.tier.host_blocks > 0) {
@@ -1179,12 +1216,11 @@ hipError_t copy(const CopyPlan& p, const CopyScratch& sc, uint8_t* cache, int64_
         const int64_t room = work_item_limit(threads) - a.host_wgs;
         grid = (grid < room ? grid : room) + a.host_wgs;
     }
-    if (p.lbase)
-        hipLaunchKernelGGL(k_copy_spans<GATHER>, dim3((unsigned)grid), dim3(threads), 0, s, a);
-    else if (GATHER)
-        hipLaunchKernelGGL(k_copy_slices, dim3((unsigned)grid), dim3(threads), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_copy_pairs, dim3((unsigned)grid), dim3(threads), 0, s, a);
+    const bool tiered = p.tier.host_blocks > 0;
+    auto* kernel = p.lbase  ? (tiered ? k_copy_spans_tiered<GATHER> : k_copy_spans<GATHER>)
+                   : GATHER ? (tiered ? k_copy_slices_tiered : k_copy_slices)
+                            : (tiered ? k_copy_pairs_tiered : k_copy_pairs);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1201,6 +1237,7 @@ hipError_t launch_copy_rows(const CopyPlan& p, const Pair* pairs, const unsigned
     a.block_bytes = p.block_bytes;
     a.chunk_bytes = p.chunk_bytes;
     a.chunks_per_block = p.chunks_per_block;
+    a.threads = p.threads;
     int64_t grid = (int64_t)p.loop_grid;
     const int64_t bound = max_pairs * ((p.block_bytes + kRowPiece - 1) / kRowPiece);
     if (grid > bound) grid = bound;
@@ -1292,7 +1329,7 @@ hipError_t launch_gather_copy(const CopyPlan& p, const CopyScratch& sc, uint8_t*
 hipError_t launch_gather_one(const CopyPlan& p, const int32_t* ids, const int32_t* m,
                              const int32_t* block_table, int32_t max_blocks, uint8_t* cache,
                              int64_t cache_blocks, int32_t l0, int32_t l1, hipStream_t s) {
-    CopyArgs a = copy_args(p, cache, cache_blocks, l0, l1);
+    CopyArgs a = copy_args(p, cache, cache_blocks, p.threads, l0, l1);
     a.ids = ids;
     a.table = block_table;
     a.m = m;
