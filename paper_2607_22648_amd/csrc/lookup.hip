@@ -73,9 +73,8 @@ struct Window16 {
     }
 
     // n > 0. All of a lane's loads are issued before any is waited for:
-    // pieces past the window's end (a window may lie past the request's)
-    // re-read the last piece of the request's blocks and land in LDS rows no
-    // lane reads.
+    // pieces past the window's end re-read the last piece of the request's
+    // blocks and land in LDS rows no lane reads.
     __device__ inline void stage(const int32_t* __restrict__ seq, int w0, int n, int) {
         wave_lds_sync();  // the previous window's reads are issued
         const int nq = (n - w0 < kWave ? n - w0 : kWave) * kQuads;
@@ -143,9 +142,9 @@ struct Window16 {
     }
 };
 
-// A window of blocks of any other multiple of four tokens. Its tokens pass
-// through the wave's LDS area sixteen a block at a time: four lanes read 64
-// neighbouring bytes of a row, every lane hashes its own block's part from
+// A window of blocks of another multiple of four tokens (which: through_lds).
+// Its tokens pass through the wave's LDS area sixteen a block at a time: four
+// lanes read 64 neighbouring bytes of a row, every lane hashes its own block's part from
 // LDS, and the next part's loads are under way meanwhile. The token check
 // reads the window and the stored rows again by whole lines, lane p of the
 // window's 16-byte pieces on the piece's row. Reading and comparing its own
@@ -652,13 +651,29 @@ __global__ __launch_bounds__(W * kWave) void k_lookup_wide(IndexView ix, Batch b
 }  // namespace
 
 namespace {
+// Whether windows of a multiple of four tokens pass through LDS (WindowQuads)
+// or each lane reads its own block. LDS costs half of the waves a compute unit
+// can hold and the same work for 64 rows however few a request has; it saves
+// a lane its trips to memory, one to two per token. With at most 192 tokens a
+// request and more of them than the device then holds waves (4,096), or with
+// blocks of four, there is less to save: 8,192 requests of 16 blocks of 8
+// tokens take 14.8 us through LDS and 14.1 without (none stored: 12.3 and
+// 11.0), of 4 blocks of 20 17.6 and 15.3, of 16 blocks of 4 13.8 and 10.8.
+// Past the line LDS wins: 16 blocks of 20 20.2 and 24.4, of 32 22.4 and 47.6;
+// 2,048 requests of 64 blocks of 8 7.8 and 10.4.
+bool through_lds(const IndexView& ix, const Batch& b) {
+    const int32_t bt = ix.block_tokens;
+    if (bt % 4 != 0 || bt == 4) return false;
+    return b.R <= 4096 || (int64_t)bt * b.max_blocks > 192;
+}
+
 template <int MODE, int W>
 void launch_wide(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids, const InsertMatch& im,
                  hipStream_t s) {
     const dim3 grid((unsigned)b.R), block(W * kWave);
     if (ix.block_tokens == 16)
         hipLaunchKernelGGL((k_lookup_wide<16, MODE, W>), grid, block, 0, s, ix, b, m, ids, im);
-    else if (ix.block_tokens % 4 == 0)
+    else if (through_lds(ix, b))
         hipLaunchKernelGGL((k_lookup_wide<kFours, MODE, W>), grid, block, 0, s, ix, b, m, ids, im);
     else
         hipLaunchKernelGGL((k_lookup_wide<0, MODE, W>), grid, block, 0, s, ix, b, m, ids, im);
@@ -681,7 +696,7 @@ hipError_t launch(const IndexView& ix, const Batch& b, int32_t* m, int32_t* ids,
     const unsigned grid = (unsigned)((b.R + kWavesPerGroup - 1) / kWavesPerGroup);
     if (ix.block_tokens == 16)
         hipLaunchKernelGGL((k_lookup<16, MODE>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids, im);
-    else if (ix.block_tokens % 4 == 0)
+    else if (through_lds(ix, b))
         hipLaunchKernelGGL((k_lookup<kFours, MODE>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids, im);
     else
         hipLaunchKernelGGL((k_lookup<0, MODE>), dim3(grid), dim3(kThreads), 0, s, ix, b, m, ids, im);

@@ -52,3 +52,28 @@ def test_windows_of_any_block(bt, maxb):
     t.lookup(*pack(reqs), maxb)
     t.check_meta()
     t.close()
+
+
+@pytest.mark.parametrize("bt,maxb", [(4, 4), (4, 60), (8, 4), (8, 24), (8, 25), (12, 16), (20, 9), (20, 10), (64, 3)])
+@pytest.mark.parametrize("R", [4096, 4097])
+def test_many_short_requests(R, bt, maxb):
+    """Both sides of the rule that takes many requests of few tokens past LDS: more than 4,096
+    requests, room for at most 192 tokens each, blocks of four tokens. Stored, cut and fresh
+    requests, ragged ends, requests that share their blocks with another of the batch."""
+    rng = np.random.default_rng(R + 100 * bt + maxb)
+    docs = rng.integers(0, 9, size=(40, maxb * bt), dtype=np.int32)
+    rows = []
+    for i in range(R):
+        d = docs[rng.integers(0, 40)][:int(rng.integers(0, maxb * bt + 1))].copy()
+        if d.size and i % 3 == 0:
+            d[rng.integers(0, d.size)] += 50 + i % 7
+        rows.append(d)
+    offs = np.zeros(R + 1, dtype=np.int64)
+    offs[1:] = np.cumsum([len(r) for r in rows])
+    toks = np.concatenate(rows).astype(np.int32)
+    t = Twin(1, 1, 8, bt, 40_000, payload=False)
+    t.insert(docs.reshape(-1), np.arange(41, dtype=np.int64) * (maxb * bt), maxb)
+    t.lookup(toks, offs, maxb)
+    t.insert(toks, offs, maxb)
+    t.lookup(toks, offs, maxb)
+    t.close()
