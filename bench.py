@@ -654,13 +654,13 @@ def run_tiered(args, torch, P, synth, dev):
         # the path is bound by the host link: the copy kernel's reads of
         # host-tier rows, their bytes per step over the time the link carries
         # them, against the link's published peak
-        "roofline": {"bound": "host link", "kernel": "k_copy_slices (gather, host-tier rows)",
+        "roofline": {"bound": "host link", "kernel": "k_copy_slices_tiered (gather, host-tier rows)",
                      "achieved": hl, "peak": HOST_LINK_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(hl / HOST_LINK_PEAK_GBPS, 4) if hl else None, "traffic": None,
                      "bytes_per_step": b["host_GB_per_step"] * 1e9,
                      "frac_of_measured_link_ceiling": round(hl / link["read_GBps"], 4) if hl else None},
         # every gather launch of a step (host-tier and device rows) against HBM
-        "gather_all_launches": roofline("k_copy_slices (gather)", gather_bytes_step / len(subs),
+        "gather_all_launches": roofline("k_copy_slices_tiered (gather)", gather_bytes_step / len(subs),
                                         b["_g_ms"] / max(b["gather_launches"], 1),
                                         b["gather_launches"], None),
         "host_link": {"achieved": hl, "ceiling": link["read_GBps"],
